@@ -204,6 +204,7 @@ struct dmpt_ctx {
   dmpt_precision prec;
   int64_t n, nocc, np, ld;
   int ftile[kMaxK + 1];   // split forms: tile edge of the fused launch for k responses
+  DirectTile dtile[kMaxK + 1];   // direct forms: tiling of the products for k responses
   int k_max, max_layers, poll, check_sym;
   hipStream_t stream;
   LayerState* st;
@@ -245,6 +246,7 @@ struct dmpt_ctx {
   void* t3[kMaxK];                 // Sh1_j S1_j + S1_j Sh1_j
   LayerState* st_rep;              // replay state
   TileItem* adj_items[4];          // outputs 1 .. 1 + 2k of the adjoint products, k = 1..3
+  DirectTile adj_tile[4];          // their tiling
   int adj_n_items[4];
   int last_k;                      // k of the last response (0: none)
   DevAlloc mem;
@@ -417,9 +419,12 @@ dmpt_status dmpt_init(dmpt_ctx** out, const double* H0, int64_t N, int64_t Nocc,
       get(&c->t3[j], mat * eb);
     }
     get((void**)&c->st_rep, sizeof(LayerState));
-    const int Ta = (int)(c->np / product_tile(c->prec == DMPT_FP64 ? DMPT_FP64 : DMPT_FP32));
+    const dmpt_precision aprec = c->prec == DMPT_FP64 ? DMPT_FP64 : DMPT_FP32;
     for (int k = 1; k <= 3 && k <= k_max; ++k) {
-      std::vector<TileItem> items = build_items_all_tiles(Ta, 1 + 2 * k);
+      // (the tiles cover all np rows: the segment store is not cleared)
+      c->adj_tile[k] = direct_tile(aprec, c->np, 1 + 2 * k, 0, false);
+      std::vector<TileItem> items =
+          build_items_all_tiles((int)(c->np / c->adj_tile[k].edge), 1 + 2 * k);
       c->adj_n_items[k] = (int)items.size();
       get((void**)&c->adj_items[k], items.size() * sizeof(TileItem));
       if (e == hipSuccess)
@@ -439,13 +444,19 @@ dmpt_status dmpt_init(dmpt_ctx** out, const double* H0, int64_t N, int64_t Nocc,
       cus <= 0)
     cus = 256;
   for (int k = 1; k <= k_max; ++k) {
-    // split forms: the fused launch's tile and its rounds balanced over its
-    // workgroups (the 256-row launch runs one per CU, the 128-row one two)
-    c->ftile[k] = split ? fused_tile(N, k, cus, c->ckpt > 0) : tile;
-    const int T = split ? (int)((N + c->ftile[k] - 1) / c->ftile[k]) : (int)(c->np / tile);
-    const int fgrid = c->ftile[k] == 128 ? 2 * cus : cus;
-    std::vector<TileItem> items = split ? balanced_items(build_items(T, k), fgrid)
-                                        : build_items(T, k);
+    // the launch's tile edge, its tiles and their rounds balanced over its
+    // workgroups (split forms: one workgroup per CU of the 256-row launch, two
+    // of the 128-row one).  Direct forms of a context with checkpoints cover
+    // all np rows: the adjoint's segment store is not cleared.
+    if (split)
+      c->ftile[k] = fused_tile(N, k, cus, c->ckpt > 0);
+    else
+      c->dtile[k] = direct_tile(c->prec, N, 1, k, true);
+    const int edge = split ? c->ftile[k] : c->dtile[k].edge;
+    const int per_cu = split ? (edge == 128 ? 2 : 1) : c->dtile[k].per_cu;
+    const int64_t rows = !split && c->ckpt ? c->np : N;
+    const int T = (int)((rows + edge - 1) / edge);
+    std::vector<TileItem> items = balanced_items(build_items(T, k), per_cu * cus);
     c->n_items[k] = (int)items.size();
     get((void**)&c->items[k], items.size() * sizeof(TileItem));
     if (e == hipSuccess)
@@ -590,6 +601,8 @@ dmpt_status run_response(dmpt_ctx* c, const double* const* H1, int k1, bool orde
     pa.state = c->st;
     pa.ld = ld;
     pa.kdim = np;
+    pa.kext = direct_kext(c->n);
+    pa.tile = c->dtile[k];
     pa.s1b[0] = c->s1buf[0][0];
     pa.s1b[1] = c->s1buf[0][1];
   }
@@ -810,6 +823,8 @@ dmpt_status dmpt_adjoint(dmpt_ctx* c, const double* const* W, int32_t k, const d
   fa.state = c->st_rep;
   fa.ld = ld;
   fa.kdim = np;
+  fa.kext = direct_kext(c->n);
+  fa.tile = c->dtile[k];
   fa.lo_shift = t;
 
   ProductArgs ba;                     // adjoint products: T2, T1_j, T3_j
@@ -820,6 +835,8 @@ dmpt_status dmpt_adjoint(dmpt_ctx* c, const double* const* W, int32_t k, const d
   ba.mode = 3;                        // one product per output on every tile
   ba.ld = ld;
   ba.kdim = np;
+  ba.kext = direct_kext(c->n);
+  ba.tile = c->adj_tile[k];
   // FP32 reverse products: one accumulator over k.  The gradients' error is
   // the forward's (split BF16 at 7e-4 against 1e-5 from these products), and
   // the blocked sums would cost 9% of the adjoint at N = 4096.
@@ -980,7 +997,9 @@ dmpt_status dmpt_layer_products(int32_t precision, int64_t N, const double* S, c
     }
   }
   get((void**)&part, kRedBlocks * sizeof(double));
-  const int T = (int)(np / tile);
+  const DirectTile dtile = direct_tile(prec, N, 1, S1 ? 1 : 0, true);
+  const int edge = split ? tile : dtile.edge;
+  const int T = (int)((N + edge - 1) / edge);
   std::vector<TileItem> it = build_items(T, S1 ? 1 : 0);
   get(&items, it.size() * sizeof(TileItem));
   if (e != hipSuccess) {
@@ -1022,6 +1041,8 @@ dmpt_status dmpt_layer_products(int32_t precision, int64_t N, const double* S, c
   pa.state = nullptr;
   pa.ld = ld;
   pa.kdim = np;
+  pa.kext = direct_kext(N);
+  pa.tile = dtile;
   pa.lo_shift = t;
   if (S1) {
     pa.s1_hi[0] = split ? th : tm;

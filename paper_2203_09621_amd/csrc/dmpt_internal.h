@@ -119,6 +119,11 @@ struct ProblemDesc {
   int64_t pdim;              // panel-layout size of the 16-bit operands (multiple of 256)
 };
 
+// Tiling of a direct-form product launch: tile edge and workgroups per CU.
+struct DirectTile {
+  int32_t edge, per_cu;
+};
+
 // Pointers of the layer products.  The product kernels read `state` to skip
 // outputs whose order has converged and to find the S1 split scales.
 struct ProductArgs {
@@ -149,7 +154,9 @@ struct ProductArgs {
   int32_t plain_accum;       // FP32 direct form: nonzero runs one accumulator over the whole
                              // k range instead of blocked sums (faster, less accurate; the
                              // adjoint's reverse products, whose error the forward dominates)
-  int32_t pad1;
+  DirectTile tile;           // direct forms: tiling of `items` (direct_tile)
+  int64_t kext;              // direct forms: k extent of the products, N rounded up to 64 (the
+                             // operands are zero from N on, so every k past N adds exact zeros)
 };
 
 // ----------------------------------------------------------------- launchers
@@ -164,6 +171,10 @@ int product_tile(dmpt_precision prec);   // output tile edge used by the product
 // the item index or -1; the plain order when n <= grid or when the result
 // would exceed `limit` positions.
 std::vector<int32_t> balanced_rounds(const std::vector<int64_t>& cost, int grid, size_t limit);
+// Tiling of a direct-form launch over `singles` outputs of one product and
+// `doubles` outputs of two, on the upper tiles or on every tile.
+DirectTile direct_tile(dmpt_precision prec, int64_t n, int singles, int doubles, bool upper);
+inline int64_t direct_kext(int64_t n) { return (n + 63) / 64 * 64; }
 hipError_t launch_products(dmpt_precision prec, const ProductArgs& a, hipStream_t s);
 // Tile items of an Np x Np output for the single-product modes: upper tiles
 // (mode 1) or all tiles (mode 2), tile edge product_tile(prec).

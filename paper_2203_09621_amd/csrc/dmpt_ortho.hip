@@ -83,6 +83,7 @@ struct ProductWork {
   TileItem* items_sym = nullptr;
   TileItem* items_all = nullptr;
   int n_sym = 0, n_all = 0;
+  DirectTile tile_sym{}, tile_all{};
   double* part = nullptr;
   double* dscal = nullptr;
 
@@ -104,12 +105,15 @@ struct ProductWork {
     np = (n + tile - 1) / tile * tile;
     ld = np;
     eb = prec == DMPT_FP64 ? 8 : 4;
-    const int T = (int)(np / tile);
-    n_sym = T * (T + 1) / 2;
-    n_all = T * T;
+    tile_sym = direct_tile(prec, n, 1, 0, true);
+    tile_all = direct_tile(prec, n, 1, 0, false);
+    const int Ts = (int)((n + tile_sym.edge - 1) / tile_sym.edge);
+    const int Ta = (int)((n + tile_all.edge - 1) / tile_all.edge);
+    n_sym = Ts * (Ts + 1) / 2;
+    n_all = Ta * Ta;
     std::vector<TileItem> sym(n_sym), all(n_all);
-    product_items(T, 1, sym.data());
-    product_items(T, 2, all.data());
+    product_items(Ts, 1, sym.data());
+    product_items(Ta, 2, all.data());
     hipError_t e = get((void**)&items_sym, sym.size() * sizeof(TileItem));
     if (e == hipSuccess) e = get((void**)&items_all, all.size() * sizeof(TileItem));
     if (e == hipSuccess)
@@ -131,6 +135,8 @@ struct ProductWork {
     a.n_items = symmetric ? n_sym : n_all;
     a.ld = ld;
     a.kdim = np;
+    a.kext = direct_kext(n);
+    a.tile = symmetric ? tile_sym : tile_all;
     a.mode = symmetric ? 1 : 2;
     return launch_products(prec, a, s);
   }

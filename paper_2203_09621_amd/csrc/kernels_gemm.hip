@@ -19,6 +19,8 @@
 // uses the same order.
 #include <stdlib.h>
 
+#include <algorithm>
+
 #include "layer_common.h"
 
 namespace dmpt {
@@ -1039,7 +1041,8 @@ template <> struct Direct<double> {
 // reads one 16-byte chunk (E consecutive k) per fragment and issues E MFMAs,
 // the e-th taking element e; A and B use the same (lane group, e) -> k map.
 // WPE waves per SIMD (4 WPE / (WGM WGN) workgroups per CU).  Operands go
-// straight from global memory into LDS, two stages of BK-wide k-tiles.
+// straight from global memory into LDS, STAGES stages of BK-wide k-tiles: the
+// loads of tile t + STAGES - 1 go out while tile t is multiplied.
 //
 // FLUSH > 0: blocked accumulation.  The FP32 16x16x4 MFMA adds its four
 // products one at a time, each rounded to FP32 and then added with one more
@@ -1048,7 +1051,7 @@ template <> struct Direct<double> {
 // FLUSH k-tiles from zero, and that partial sum is added to a second
 // accumulator (one FP32 addition) before the next chunk starts: the error of
 // a long sum then grows with FLUSH BK + kdim / (FLUSH BK) instead of kdim.
-template <typename T, int BM, int BK, int WGM, int WGN, int SWZ, int WPE, int FLUSH = 0>
+template <typename T, int BM, int BK, int WGM, int WGN, int SWZ, int WPE, int STAGES, int FLUSH = 0>
 __global__ void __launch_bounds__(WGM * WGN * kWave) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 k_products_direct(const ProductArgs a) {
   using D = Direct<T>;
@@ -1110,34 +1113,42 @@ k_products_direct(const ProductArgs a) {
   }
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
-  const int wave = tid / kWave;
+  const int wave = uni(tid / kWave);
   const int wm = wave / WGN, wn = wave % WGN;
   const int lrow = tid / CH, lch = tid % CH;
   const int64_t row_a0 = (int64_t)it.ti * BM, row_b0 = (int64_t)it.tj * BN;
-  const int kt_per = (int)(a.kdim / BK);
+  const int kt_per = uni((int)(a.kext / BK));
   const int ktiles = nprod * kt_per;
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    Q0[r] = uni(Q0[r]);
+    Q1[r] = uni(Q1[r]);
+    Q2[r] = uni(Q2[r]);
+  }
 
   // In load round i, lane l of wave w writes 16-byte slot l of the wave's
   // 1 KB block (global_load_lds_dwordx4), i.e. row i * RPL + lrow, slot lch,
   // so it fetches the chunk whose swizzled position that slot is; the swizzle
-  // of a row does not depend on i.
+  // of a row does not depend on i, so a round adds only a wave-uniform offset.
   static_assert(((RPL >> SWZ) % CH) == 0, "swizzle must repeat every load round");
   static_assert(kWave % CH == 0, "a wave fills whole rows");
-  const int wave_u = uni(wave);
   const int csrc = lch ^ ((lrow >> SWZ) & (CH - 1));
-  auto issue = [&](int t) {
-    const int p = t / kt_per;
+  const int64_t voff = lrow * ld + csrc * E;
+  // Tile t of the concatenated k range; past the end the last tile is fetched
+  // again into a stage nobody reads any more, so every iteration issues the
+  // same number of loads and the waits can count them.
+  auto issue = [&](int t0) {
+    const int t = t0 < ktiles ? t0 : ktiles - 1;
+    const int p = (t >= kt_per) + (t >= 2 * kt_per);
     const int64_t k0 = (int64_t)(t - p * kt_per) * BK;
-    u32x4* stage = lds + (t & 1) * STAGE;
+    u32x4* stage = lds + (t0 % STAGES) * STAGE;
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {
       const int arr = (i * RPL) / BM;             // compile-time after unrolling
-      const int r = i * RPL - arr * BM + lrow;
-      const int64_t grow = (arr == 0 ? row_a0 : row_b0) + r;
-      const T* basep = p == 0 ? Q0[arr] : (p == 1 ? Q1[arr] : Q2[arr]);
-      const T* src = basep + grow * ld + k0 + csrc * E;
-      u32x4* dst = stage + (i * RPL + wave_u * (kWave / CH)) * CH;     // wave-uniform
-      __builtin_amdgcn_global_load_lds((const void*)src, (void*)dst, 16, 0, 0);
+      const int64_t row = (arr == 0 ? row_a0 : row_b0) + (i * RPL - arr * BM);
+      const T* basep = (p == 0 ? Q0[arr] : (p == 1 ? Q1[arr] : Q2[arr])) + row * ld + k0;
+      u32x4* dst = stage + (i * RPL + wave * (kWave / CH)) * CH;       // wave-uniform
+      __builtin_amdgcn_global_load_lds((const void*)(basep + voff), (void*)dst, 16, 0, 0);
     }
   };
 
@@ -1169,55 +1180,81 @@ k_products_direct(const ProductArgs a) {
         }
   };
 
-  issue(0);
-  __builtin_amdgcn_s_waitcnt(VmWait<0>::imm);
-  __syncthreads();
-  for (int t = 0; t < ktiles; ++t) {
-    const int cur = t & 1;
-    // tile t + 1 goes to the stage that tile t - 1 used (every wave has left it)
-    if (t + 1 < ktiles) issue(t + 1);
-    const u32x4* base = lds + cur * STAGE;
+  // Fragments of one step of four chunks: 16-byte chunk 4 kk + lane / 16 of
+  // the wave's rows of A and B.
+  struct Frag { u32x4 a[FM], b[FN]; };
+  constexpr int KK = CH / 4;
+  auto read = [&](int t, int kk, Frag& f) {
+    const u32x4* base = lds + (t % STAGES) * STAGE;
+    const int c = kk * 4 + (lane >> 4);
 #pragma unroll
-    for (int kk = 0; kk < CH / 4; ++kk) {
-      const int c = kk * 4 + (lane >> 4);
-      u32x4 af[FM], bf[FN];
-#pragma unroll
-      for (int m = 0; m < FM; ++m) {
-        const int R = wm * WTM + m * 16 + (lane & 15);
-        af[m] = base[R * CH + (c ^ ((R >> SWZ) & (CH - 1)))];
-      }
-#pragma unroll
-      for (int n = 0; n < FN; ++n) {
-        const int R = BM + wn * WTN + n * 16 + (lane & 15);
-        bf[n] = base[R * CH + (c ^ ((R >> SWZ) & (CH - 1)))];
-      }
-      // Accumulators in groups of GRP, each group through all E elements
-      // before the next: the FP64 16x16x4 MFMA keeps about 90% of its rate
-      // with four accumulators in turn and 72% with sixteen (FP32 keeps full
-      // rate either way).  Every accumulator still takes its k in order.
-      constexpr int GRP = sizeof(T) == 8 ? 4 : FM * FN;
-      static_assert((FM * FN) % GRP == 0, "whole groups");
-      typedef T TV __attribute__((ext_vector_type(E)));
-#pragma unroll
-      for (int g0 = 0; g0 < FM * FN; g0 += GRP) {
-#pragma unroll
-        for (int e = 0; e < E; ++e)
-#pragma unroll
-          for (int q = g0; q < g0 + GRP; ++q) {
-            const int m = q / FN, n = q % FN;
-            acc[m][n] = D::mma(__builtin_bit_cast(TV, af[m])[e], __builtin_bit_cast(TV, bf[n])[e],
-                               acc[m][n]);
-          }
-        // (the scheduler would interleave the groups again)
-        if constexpr (GRP < FM * FN) __builtin_amdgcn_sched_barrier(0);
-      }
+    for (int m = 0; m < FM; ++m) {
+      const int R = wm * WTM + m * 16 + (lane & 15);
+      f.a[m] = base[R * CH + (c ^ ((R >> SWZ) & (CH - 1)))];
     }
+#pragma unroll
+    for (int n = 0; n < FN; ++n) {
+      const int R = BM + wn * WTN + n * 16 + (lane & 15);
+      f.b[n] = base[R * CH + (c ^ ((R >> SWZ) & (CH - 1)))];
+    }
+  };
+  // Accumulators in groups of GRP, each group through all E elements before
+  // the next: the FP64 16x16x4 MFMA keeps about 90% of its rate with four
+  // accumulators in turn and 72% with sixteen (FP32 keeps full rate either
+  // way).  Every accumulator still takes its k in order.
+  constexpr int GRP = sizeof(T) == 8 && FM * FN > 4 ? 4 : FM * FN;
+  static_assert((FM * FN) % GRP == 0, "whole groups");
+  auto mma = [&](const Frag& f) {
+    typedef T TV __attribute__((ext_vector_type(E)));
+#pragma unroll
+    for (int g0 = 0; g0 < FM * FN; g0 += GRP) {
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+#pragma unroll
+        for (int q = g0; q < g0 + GRP; ++q) {
+          const int m = q / FN, n = q % FN;
+          acc[m][n] = D::mma(__builtin_bit_cast(TV, f.a[m])[e], __builtin_bit_cast(TV, f.b[n])[e],
+                             acc[m][n]);
+        }
+      // (the scheduler would interleave the groups again)
+      if constexpr (GRP < FM * FN) __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  // The fragments of the next step are read while this one is multiplied,
+  // across k-tiles too: the one barrier per k-tile sits before its last step.
+  // By then every wave holds that step's fragments (tile t's stage may be
+  // refilled) and every wave's loads of tile t + 1 have landed (loads complete
+  // in order; the STAGES - 2 tiles after it may be outstanding).
+  static_assert(KK % 2 == 0, "fragment sets alternate");
+  Frag f[2];
+#pragma unroll
+  for (int t = 0; t < STAGES; ++t) issue(t);
+  __builtin_amdgcn_s_waitcnt(VmWait<(STAGES - 1) * LOADS>::imm);
+  lds_barrier();
+  read(0, 0, f[0]);
+  for (int t = 0; t < ktiles; ++t) {
+    // FP32 128-row tiles: the compiler's interleave of LDS reads and MFMAs for
+    // small products (3.05 ms per adjoint launch at N = 4096 against 3.26 ms
+    // with its default order; the other tilings lose or gain under 2%)
+    if constexpr (sizeof(T) == 4 && BM == 128) __builtin_amdgcn_iglp_opt(0);
+#pragma unroll
+    for (int kk = 0; kk < KK - 1; ++kk) {
+      read(t, kk + 1, f[(kk + 1) & 1]);
+      mma(f[kk & 1]);
+    }
+    __builtin_amdgcn_s_waitcnt(VmWait<(STAGES - 2) * LOADS>::imm);
+    lds_barrier();
+    issue(t + STAGES);
+    read(t + 1, 0, f[0]);
+    mma(f[1]);
     if constexpr (FLUSH > 0) {
       if ((t + 1) % FLUSH == 0 || t + 1 == ktiles) flush();
     }
-    __builtin_amdgcn_s_waitcnt(VmWait<0>::imm);   // this wave's part of tile t + 1
-    __syncthreads();
   }
+  // the refetches past the end land before the LDS is reused
+  __builtin_amdgcn_s_waitcnt(VmWait<0>::imm);
+  lds_barrier();
   if constexpr (FLUSH > 0) {
 #pragma unroll
     for (int m = 0; m < FM; ++m)
@@ -1252,34 +1289,41 @@ k_products_direct(const ProductArgs a) {
 // ------------------------------------------------------------------ dispatch
 // Tile configurations (edge, k-tile, wave grid, LDS swizzle shift).
 constexpr int kSplitBM = 256, kSplitWGM = 2, kSplitWGN = 2;
-// 128 x 128 tiles, 16-wide k-tiles.  FP32: 4 waves of 64 x 64 per workgroup
-// (32 KB of LDS); with the blocked accumulation (a second set of 64
-// accumulators, 194 registers) two waves per SIMD and two workgroups per CU,
-// without it four and four.  FP64: 8 waves of 64 x 32 (64 KB), two
-// workgroups per CU, four waves per SIMD; its 16x16x4 MFMA keeps its rate
-// only with few accumulators in turn, so a wave holds eight.
-constexpr int kDirBM = 128, kDirWGM = 2;
-constexpr int kDirBK32 = 16, kDirSWZ32 = 2, kDirWGN32 = 2, kDirWG32 = 4;
-constexpr int kDirBK64 = 16, kDirSWZ64 = 1, kDirWGN64 = 4, kDirWG64 = 2;
-// FP32: the MFMAs accumulate 4 k-tiles (64 k) before the partial sum joins the
-// running total; the second set of accumulators takes two waves per SIMD.
-constexpr int kDirFlush32 = 4;
+// Direct forms (launch_products): per tile edge and workgroups per CU, the
+// wave grid, k-tile, LDS swizzle shift and stages.  128 x 128: 8 waves of 64 x
+// 32 in two stages of 32 KB, two workgroups per CU and four waves per SIMD
+// (FP64: its 16x16x4 MFMA keeps its rate only with few accumulators in turn,
+// and a wave holds eight; FP32: the adjoint's products at N = 4096 take 3.05
+// ms per launch against 3.23 ms with 4 waves of 64 x 64, four workgroups per CU
+// and 16-wide k-tiles, whose registers hold one set of fragments).  64 and 32:
+// waves of 32 x 32 (32 x 16 in FP64 with two workgroups per CU) and 16 x 16,
+// k-tiles of 16 to 64 in two to four stages of 16 or 32 KB, and as many
+// workgroups per CU as the LDS then holds (one where a launch has about one
+// item per CU: with room for two, the dispatcher stacks them on some CUs and
+// leaves others idle).
+// The FP32 MFMAs accumulate 64 k before the partial sum joins the running
+// total (FLUSH = 64 / BK); the order of every accumulator's k is the same for
+// every tile edge, so the results are too.
+constexpr int kDirBM = 128;
+constexpr int kDirFlushK = 64;
 
 int product_tile(dmpt_precision prec) {
   return (prec == DMPT_SPLIT_FP16 || prec == DMPT_SPLIT_BF16) ? kSplitBM : kDirBM;
 }
 
 void product_items(int T, int mode, TileItem* out) {
+  // bands of 8 tile rows walked column by column: items side by side share panels
   int k = 0;
-  for (int ti = 0; ti < T; ++ti)
-    for (int tj = mode == 2 ? 0 : ti; tj < T; ++tj) {
-      TileItem it;
-      it.out = 0;
-      it.prob = 0;
-      it.ti = ti;
-      it.tj = tj;
-      out[k++] = it;
-    }
+  for (int g0 = 0; g0 < T; g0 += 8)
+    for (int tj = mode == 2 ? 0 : g0; tj < T; ++tj)
+      for (int ti = g0; ti < std::min(g0 + 8, mode == 2 ? T : std::min(T, tj + 1)); ++ti) {
+        TileItem it;
+        it.out = 0;
+        it.prob = 0;
+        it.ti = ti;
+        it.tj = tj;
+        out[k++] = it;
+      }
 }
 
 static int device_cus() {
@@ -1340,6 +1384,35 @@ static hipError_t launch_split_pair(const ProductArgs& a, hipStream_t s) {
   return launch_one(k_products_pair<T16, 2>, 8 * kWave, lds, 1, a, s);
 }
 
+template <typename T, int BM, int BK, int WGM, int WGN, int SWZ, int PER_CU, int STAGES,
+          int FLUSH = 0>
+static hipError_t launch_direct(const ProductArgs& a, hipStream_t s) {
+  constexpr size_t lds = (size_t)STAGES * 2 * BM * BK * sizeof(T);
+  constexpr int WPE = PER_CU * WGM * WGN / 4;
+  static_assert(PER_CU * lds <= 160 * 1024 - 256, "LDS of one CU");
+  return launch_one(k_products_direct<T, BM, BK, WGM, WGN, SWZ, WPE, STAGES, FLUSH>,
+                    WGM * WGN * kWave, lds, PER_CU, a, s);
+}
+
+// BLOCKED: the accumulation in blocks of kDirFlushK
+template <bool BLOCKED>
+static hipError_t launch_direct32(const ProductArgs& a, hipStream_t s) {
+  constexpr int F = BLOCKED ? kDirFlushK : 0;
+  if (a.tile.edge == 128 && a.tile.per_cu == 2)
+    return launch_direct<float, 128, 32, 2, 4, 1, 2, 2, F / 32>(a, s);
+  if (a.tile.edge == 64 && a.tile.per_cu == 3)
+    return launch_direct<float, 64, 32, 2, 2, 1, 3, 3, F / 32>(a, s);
+  if (a.tile.edge == 64 && a.tile.per_cu == 2)
+    return launch_direct<float, 64, 64, 2, 2, 0, 2, 2, F / 64>(a, s);
+  if (a.tile.edge == 64 && a.tile.per_cu == 1)
+    return launch_direct<float, 64, 64, 2, 2, 0, 1, 3, F / 64>(a, s);
+  if (a.tile.edge == 32 && a.tile.per_cu == 4)
+    return launch_direct<float, 32, 64, 2, 2, 0, 4, 2, F / 64>(a, s);
+  if (a.tile.edge == 32 && a.tile.per_cu == 2)
+    return launch_direct<float, 32, 64, 2, 2, 0, 2, 4, F / 64>(a, s);
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_products_pair(dmpt_precision prec, const ProductArgs& a, hipStream_t s) {
   if (!a.probs || !a.part_f || !a.part_m) return hipErrorInvalidValue;
   if (prec == DMPT_SPLIT_FP16) return launch_split_pair<_Float16>(a, s);
@@ -1364,25 +1437,30 @@ hipError_t launch_products(dmpt_precision prec, const ProductArgs& a, hipStream_
     return hipErrorInvalidValue;
   if (a.mode != 0 && (prec == DMPT_SPLIT_FP16 || prec == DMPT_SPLIT_BF16 || a.state))
     return hipErrorInvalidValue;               // single products: direct forms, no state
+  if ((prec == DMPT_FP32 || prec == DMPT_FP64) &&
+      (a.kext <= 0 || a.kext > a.kdim || a.kext % kDirFlushK != 0))
+    return hipErrorInvalidValue;
   switch (prec) {
     case DMPT_SPLIT_FP16:
       return launch_split<_Float16, false>(a, s);
     case DMPT_SPLIT_BF16:
       return launch_split<__bf16, false>(a, s);
-    case DMPT_FP32: {
-      constexpr size_t lds = 2 * (2 * kDirBM) * (kDirBK32 / 4) * 16;
-      if (a.plain_accum)
-        return launch_one(k_products_direct<float, kDirBM, kDirBK32, kDirWGM, kDirWGN32, kDirSWZ32, 4>,
-                          kDirWGM * kDirWGN32 * kWave, lds, kDirWG32, a, s);
-      return launch_one(k_products_direct<float, kDirBM, kDirBK32, kDirWGM, kDirWGN32, kDirSWZ32,
-                                          2, kDirFlush32>,
-                        kDirWGM * kDirWGN32 * kWave, lds, kDirWG32 / 2, a, s);
-    }
-    case DMPT_FP64: {
-      constexpr size_t lds = 2 * (2 * kDirBM) * (kDirBK64 / 2) * 16;
-      return launch_one(k_products_direct<double, kDirBM, kDirBK64, kDirWGM, kDirWGN64, kDirSWZ64, 4>,
-                        kDirWGM * kDirWGN64 * kWave, lds, kDirWG64, a, s);
-    }
+    case DMPT_FP32:
+      return a.plain_accum ? launch_direct32<false>(a, s) : launch_direct32<true>(a, s);
+    case DMPT_FP64:
+      if (a.tile.edge == 128 && a.tile.per_cu == 2)
+        return launch_direct<double, 128, 16, 2, 4, 1, 2, 2>(a, s);
+      if (a.tile.edge == 64 && a.tile.per_cu == 3)
+        return launch_direct<double, 64, 16, 2, 2, 1, 3, 3>(a, s);
+      if (a.tile.edge == 64 && a.tile.per_cu == 2)
+        return launch_direct<double, 64, 32, 2, 4, 0, 2, 2>(a, s);
+      if (a.tile.edge == 64 && a.tile.per_cu == 1)
+        return launch_direct<double, 64, 32, 2, 2, 0, 1, 3>(a, s);
+      if (a.tile.edge == 32 && a.tile.per_cu == 4)
+        return launch_direct<double, 32, 32, 2, 2, 0, 4, 2>(a, s);
+      if (a.tile.edge == 32 && a.tile.per_cu == 2)
+        return launch_direct<double, 32, 32, 2, 2, 0, 2, 4>(a, s);
+      break;
   }
   return hipErrorInvalidValue;
 }
@@ -1693,5 +1771,37 @@ hipError_t launch_mfma_rate(dmpt_precision prec, int blocks, int iters, float* o
 }
 
 int device_cu_count() { return device_cus(); }
+
+// One launch ends with its busiest workgroup slot: its load in items of one
+// product, max(ceil(units / slots), 2 ceil(items of two / slots)) in balanced
+// rounds, times the time such an item takes per k while every slot is busy.
+// Those times (ns per k; products of N = 1001 to 4096, one box) put the lines
+// between the tile edges.  Large tiles load less and win where there are many
+// rounds of them; small ones fill the chip below that.  Measured, us per
+// launch, FP64 with one response, 128-row tiles against the choice: N = 256:
+// 78 / 14; 512: 142 / 31; 1001: 269 / 88; 2048: 982 / 509; 3000: 1471 / 1389;
+// 4096: 3919 / 3432.  FP32: N = 256: 52 / 11; 1001: 167 / 54; N = 1500 with
+// two responses: 247 / 170; 4096: 2181 / 1795.
+DirectTile direct_tile(dmpt_precision prec, int64_t n, int singles, int doubles, bool upper) {
+  struct Cand { int edge, per_cu; double t64, t32; };
+  static const Cand cand[] = {{128, 2, 240, 130}, {64, 2, 66, 35},   {64, 3, 103, 51.5},
+                              {64, 1, 39, 21.5},  {32, 4, 37, 22.5}, {32, 2, 26, 14}};
+  DirectTile best{128, 2};
+  double best_t = 0.0;
+  for (const Cand& c : cand) {
+    // (beyond these sizes a launch has tens of rounds of the larger tile)
+    if ((c.edge == 32 && n > 4096) || (c.edge == 64 && n > 8192)) continue;
+    const int64_t T = (n + c.edge - 1) / c.edge, tiles = upper ? T * (T + 1) / 2 : T * T;
+    const int64_t slots = (int64_t)device_cus() * c.per_cu;
+    auto up = [&](int64_t x) { return (x + slots - 1) / slots; };
+    const int64_t load = std::max(up((singles + 2 * doubles) * tiles), 2 * up(doubles * tiles));
+    const double t = (double)load * (prec == DMPT_FP64 ? c.t64 : c.t32);
+    if (best_t == 0.0 || t < best_t) {
+      best_t = t;
+      best = DirectTile{c.edge, c.per_cu};
+    }
+  }
+  return best;
+}
 
 }  // namespace dmpt

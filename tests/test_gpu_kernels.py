@@ -131,3 +131,32 @@ def test_fp32_products_accumulate_in_blocks(dm):
     err = np.linalg.norm(X.cpu().numpy() - ref) / np.linalg.norm(ref)
     print(f"FP32 X = S^2 at N = {n}, positive S: rel err {err:.2e}", flush=True)
     assert err < 2.5e-7
+
+
+# sizes where the direct forms take each of their tilings (32, 64 and 128 rows,
+# one to four workgroups per CU), one past a tile edge, and the smallest
+@pytest.mark.parametrize("precision,n", [
+    (p, n) for p in ("fp64", "fp32") for n in (1, 31, 33, 129, 500, 1001, 1100, 1500, 1700, 2400)
+] + [("fp64", 3100), ("fp32", 3900)])
+def test_direct_tilings_within_the_rounding_bound(dm, precision, n):
+    """X = S^2 and X1 = S S1 + S1 S on every tiling: symmetric, and within the
+    componentwise bound of the accumulation.  FP64: one rounding per
+    multiply-add over 2 n terms.  FP32: blocks of 64 k (a product and a sum
+    rounded per term), then 2 n / 64 block sums."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(n)
+    S, S1 = (torch.randn(n, n, generator=g, device="cuda", dtype=torch.float64) for _ in range(2))
+    S, S1 = S + S.T, S1 + S1.T
+    if precision == "fp32":
+        S, S1 = S.float().double(), S1.float().double()     # inputs without rounding
+    X, X1 = dm.dmpt_layer_products(S, S1, precision=precision)
+    if precision == "fp64":
+        unit = 2.0 ** -53 * (2 * n + 2)
+    else:
+        unit = 2.0 ** -24 * (65 + 2 * (n // 64 + 1) + 1)
+    a, b = S.abs(), S1.abs()
+    assert torch.equal(X, X.T) and torch.equal(X1, X1.T)
+    # (the reference product rounds in FP64 as well)
+    slack = 2.0 ** -53 * (2 * n + 2)
+    assert ((X - S @ S).abs() <= (unit + slack) * (a @ a)).all()
+    assert ((X1 - (S @ S1 + S1 @ S)).abs() <= (unit + slack) * (a @ b + b @ a)).all()
