@@ -540,6 +540,57 @@ void dmpt_destroy(dmpt_ctx* ctx) { ctx_free(ctx); }
 
 namespace {
 
+// The end of a response: traces of the outputs, the state and the statistics.
+// n: layers enqueued.
+template <typename Out>
+dmpt_status finish_response(dmpt_ctx* c, int k, bool order2, double* P0, Out slot_out, int n,
+                            dmpt_stats* stats) {
+  hipStream_t s = c->stream;
+  if (P0) HIPCHK(launch_trace(P0, c->n, c->dscal, s));
+  for (int j = 0; j < k; ++j) HIPCHK(launch_trace(slot_out(j), c->n, c->dscal + 1 + j, s));
+  HIPCHK(hipMemcpyAsync(c->hstate, c->st, sizeof(LayerState), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(c->hscal, c->dscal, 16 * sizeof(double), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  const LayerState& h = *c->hstate;
+  if (stats) {
+    memset(stats, 0, sizeof(*stats));
+    stats->layers = h.n;
+    stats->d0_layer = h.d0_layer;
+    stats->k = k;
+    stats->converged = h.converged;
+    for (int i = 1; i <= h.n && i <= kMaxLayers; ++i) stats->sigma[i - 1] = (int8_t)h.sigma[i];
+    stats->eps1 = h.eps1;
+    stats->epsN = h.epsN;
+    stats->n_s = h.n_s;
+    stats->idem0 = h.fro0;
+    stats->trace_p0 = P0 ? c->hscal[0] : 0.0;
+    for (int j = 0; j < k; ++j) {
+      stats->d1_layer[j] = h.d1_layer[j];
+      stats->idem1[j] = h.d1_layer[j] > 0 ? h.fro1[j][h.d1_layer[j]] : 0.0;
+      stats->trace_p1[j] = c->hscal[1 + j];
+    }
+    float ms = 0.f;
+    if (hipEventElapsedTime(&ms, c->ev0, c->ev1) != hipSuccess) ms = 0.f;
+    stats->ms = ms;
+    stats->x_layers = h.d0_layer > 0 ? h.d0_layer : h.n;
+    if (c->timing) {
+      // launches of layers after the stop return at once; time only layers 1..h.n
+      double tot = 0.0;
+      for (int i = 0; i < h.n && i < n; ++i) {
+        float t_ms = 0.f;
+        if (hipEventElapsedTime(&t_ms, c->pev[2 * i], c->pev[2 * i + 1]) != hipSuccess) t_ms = 0.f;
+        tot += t_ms;
+      }
+      stats->product_ms = tot;
+      stats->product_launches = std::min(h.n, n);
+    }
+  }
+  if (h.error) return fail((dmpt_status)h.error, "non-finite value or split overflow in a layer");
+  if (!h.converged) return fail(DMPT_ENOCONV, "layer cap reached before every D1 test fired");
+  c->last_k = order2 ? 0 : k;          // the adjoint covers first-order responses
+  return DMPT_OK;
+}
+
 // The layer loop of Algorithm 1 for k1 first-order responses and, with order2,
 // the second-order chain of the first perturbation in response slot k1
 // (initial matrix -H2/(eps_N - eps_1), zero when H2 is NULL; result into P2).
@@ -564,7 +615,30 @@ dmpt_status run_response(dmpt_ctx* c, const double* const* H1, int k1, bool orde
   const int split = is_split(prec) ? 1 : 0;
   const int64_t ld = c->ld, np = c->np, elems = np * ld;
 
+  // A small problem runs as one workgroup; second order, checkpoints and
+  // per-launch timing keep the layer-by-layer path, with the same results.
+  const int tiny = split && !order2 && !c->ckpt && !c->timing ? tiny_blocks(c->n, k) : 0;
+
   HIPCHK(hipEventRecord(c->ev0, s));
+  if (tiny) {
+    TinyArgs ta;
+    memset(&ta, 0, sizeof(ta));
+    ta.one.state = c->st;
+    ta.one.s_init = (const float*)c->s_init;
+    ta.one.ld = ld;
+    ta.one.nocc = (double)c->nocc;
+    ta.one.n = (int32_t)c->n;
+    ta.p0 = P0;
+    for (int j = 0; j < k; ++j) {
+      ta.h1[j] = H1[j];
+      ta.p1[j] = P1[j];
+    }
+    ta.max_layers = c->max_layers;
+    c->last_k = 0;
+    HIPCHK(launch_tiny(prec, tiny, k, ta, 1, s));
+    HIPCHK(hipEventRecord(c->ev1, s));
+    return finish_response(c, k, order2, P0, slot_out, 0, stats);
+  }
   HIPCHK(launch_reset_state(c->st, k, order2 ? k1 : -1, c->max_layers, (double)c->nocc, c->n, s));
   HIPCHK(launch_load_s0(prec, c->s_init, c->s_master, c->s_hi[0], c->s_lo[0], np, ld, t, s));
   for (int j = 0; j < k; ++j)
@@ -650,49 +724,7 @@ dmpt_status run_response(dmpt_ctx* c, const double* const* H1, int k1, bool orde
     HIPCHK(launch_copy_out(prec, c->st, j, c->s1buf[j][0], c->s1buf[j][1], ld, slot_out(j), c->n,
                            s));
   HIPCHK(hipEventRecord(c->ev1, s));
-  if (P0) HIPCHK(launch_trace(P0, c->n, c->dscal, s));
-  for (int j = 0; j < k; ++j) HIPCHK(launch_trace(slot_out(j), c->n, c->dscal + 1 + j, s));
-  HIPCHK(hipMemcpyAsync(c->hstate, c->st, sizeof(LayerState), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(c->hscal, c->dscal, 16 * sizeof(double), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
-  const LayerState& h = *c->hstate;
-  if (stats) {
-    memset(stats, 0, sizeof(*stats));
-    stats->layers = h.n;
-    stats->d0_layer = h.d0_layer;
-    stats->k = k;
-    stats->converged = h.converged;
-    for (int i = 1; i <= h.n && i <= kMaxLayers; ++i) stats->sigma[i - 1] = (int8_t)h.sigma[i];
-    stats->eps1 = h.eps1;
-    stats->epsN = h.epsN;
-    stats->n_s = h.n_s;
-    stats->idem0 = h.fro0;
-    stats->trace_p0 = P0 ? c->hscal[0] : 0.0;
-    for (int j = 0; j < k; ++j) {
-      stats->d1_layer[j] = h.d1_layer[j];
-      stats->idem1[j] = h.d1_layer[j] > 0 ? h.fro1[j][h.d1_layer[j]] : 0.0;
-      stats->trace_p1[j] = c->hscal[1 + j];
-    }
-    float ms = 0.f;
-    if (hipEventElapsedTime(&ms, c->ev0, c->ev1) != hipSuccess) ms = 0.f;
-    stats->ms = ms;
-    stats->x_layers = h.d0_layer > 0 ? h.d0_layer : h.n;
-    if (c->timing) {
-      // launches of layers after the stop return at once; time only layers 1..h.n
-      double tot = 0.0;
-      for (int i = 0; i < h.n && i < n; ++i) {
-        float t_ms = 0.f;
-        if (hipEventElapsedTime(&t_ms, c->pev[2 * i], c->pev[2 * i + 1]) != hipSuccess) t_ms = 0.f;
-        tot += t_ms;
-      }
-      stats->product_ms = tot;
-      stats->product_launches = std::min(h.n, n);
-    }
-  }
-  if (h.error) return fail((dmpt_status)h.error, "non-finite value or split overflow in a layer");
-  if (!h.converged) return fail(DMPT_ENOCONV, "layer cap reached before every D1 test fired");
-  c->last_k = order2 ? 0 : k;          // the adjoint covers first-order responses
-  return DMPT_OK;
+  return finish_response(c, k, order2, P0, slot_out, n, stats);
 }
 
 }  // namespace

@@ -276,7 +276,7 @@ __global__ void k_b_summary(const BatchProblem* P, ProblemSummary* out) {
     s.d1_layer[j] = j < b.k ? st->d1_layer[j] : 0;
     s.idem1[j] = (j < b.k && st->d1_layer[j] > 0) ? st->fro1[j][st->d1_layer[j]] : 0.0;
   }
-  out[blockIdx.x] = s;
+  out[b.h0_index] = s;
 }
 
 }  // namespace dmpt
@@ -356,6 +356,8 @@ std::vector<TileItem> pair_items(int T, int k, int prob) {
 
 }  // namespace
 
+constexpr int kTinySides = 4;
+
 struct dmpt_batch {
   int count;
   dmpt_precision prec;
@@ -364,7 +366,15 @@ struct dmpt_batch {
   int use_graph;
   hipStream_t stream;
   hipStream_t cap;
-  std::vector<BatchProblem> hp;
+  hipStream_t side[kTinySides] = {};           // the small problems' launches run beside each
+  hipEvent_t fork = nullptr, join[kTinySides] = {};   // other, one configuration per stream
+  std::vector<BatchProblem> hp;                // layer-by-layer problems first, then the
+                                               // small ones that run as one workgroup each;
+                                               // h0_index is the caller's position
+  int n_layered = 0;
+  struct TinyLaunch { int nf, k, first, count; };
+  std::vector<TinyLaunch> tiny;                // the small ones by configuration
+  TinyProblem* dtiny = nullptr;
   BatchProblem* dp = nullptr;
   std::vector<Chunk> c0, c1;
   Chunk* dc0 = nullptr;
@@ -383,6 +393,7 @@ struct dmpt_batch {
   TileItem* items[2] = {nullptr, nullptr};     // [0]: 256-row tiles, [1]: pairs of 128-row tiles
   int n_items[2] = {0, 0};
   int total_k = 0;
+  std::vector<int> k;                          // responses of the caller's problems
   int cus = 256;                               // compute units of the device
   const double** h0tab = nullptr;
   const double** h1tab = nullptr;
@@ -418,6 +429,11 @@ void batch_free(dmpt_batch* b) {
   if (b->host_tab) (void)hipHostFree(b->host_tab);
   if (b->hsum) (void)hipHostFree(b->hsum);
   if (b->cap) (void)hipStreamDestroy(b->cap);
+  for (int i = 0; i < kTinySides; ++i) {
+    if (b->side[i]) (void)hipStreamDestroy(b->side[i]);
+    if (b->join[i]) (void)hipEventDestroy(b->join[i]);
+  }
+  if (b->fork) (void)hipEventDestroy(b->fork);
   if (b->ev0) (void)hipEventDestroy(b->ev0);
   if (b->ev1) (void)hipEventDestroy(b->ev1);
   delete b;
@@ -434,12 +450,13 @@ hipError_t build_class_items(dmpt_batch* b, int threshold) {
   // their order; the range between its first and last position may hold
   // placeholders and other problems' items, which the kernels and the
   // decisions skip.
+  const int np = b->n_layered;
   std::vector<TileItem> cls[2];
   std::vector<int> first(b->count), count(b->count), which(b->count);
   std::vector<std::vector<TileItem>> own(b->count);
   std::vector<std::vector<int64_t>> own_cost(b->count);
   std::vector<int64_t> total(b->count, 0);
-  for (int p = 0; p < b->count; ++p) {
+  for (int p = 0; p < np; ++p) {
     const BatchProblem& bp = b->hp[p];
     const int c = bp.np <= threshold ? 1 : 0;
     const int tile = c ? 128 : 256;
@@ -453,7 +470,7 @@ hipError_t build_class_items(dmpt_batch* b, int threshold) {
   }
   for (int c = 0; c < 2; ++c) {
     std::vector<int> probs;
-    for (int p = 0; p < b->count; ++p)
+    for (int p = 0; p < np; ++p)
       if (which[p] == c) probs.push_back(p);
     std::stable_sort(probs.begin(), probs.end(), [&](int x, int y) { return total[x] > total[y]; });
     std::vector<TileItem> list;
@@ -539,8 +556,8 @@ hipError_t build_class_items(dmpt_batch* b, int threshold) {
       e = hipMemcpy(b->items[c], cls[c].data(), cls[c].size() * sizeof(TileItem),
                     hipMemcpyHostToDevice);
   if (e != hipSuccess) return e;
-  std::vector<ProblemDesc> d(b->count);
-  for (int p = 0; p < b->count; ++p) {
+  std::vector<ProblemDesc> d(np);
+  for (int p = 0; p < np; ++p) {
     BatchProblem& bp = b->hp[p];
     bp.items = b->items[which[p]] + first[p];
     bp.n_items = count[p];
@@ -564,7 +581,7 @@ hipError_t build_class_items(dmpt_batch* b, int threshold) {
     q.kdim = (bp.n + kPanelK - 1) / kPanelK * kPanelK;
     q.pdim = bp.np;
   }
-  e = hipMemcpy(b->desc, d.data(), b->count * sizeof(ProblemDesc), hipMemcpyHostToDevice);
+  if (np > 0) e = hipMemcpy(b->desc, d.data(), np * sizeof(ProblemDesc), hipMemcpyHostToDevice);
   if (e == hipSuccess)
     e = hipMemcpy(b->dp, b->hp.data(), sizeof(BatchProblem) * b->count, hipMemcpyHostToDevice);
   return e;
@@ -593,21 +610,49 @@ hipError_t launch_products_all(dmpt_batch* b, hipStream_t s) {
   return e;
 }
 
+// Every input is read before an output is written: the small problems leave
+// FP32 masters like the others.
 template <typename T16>
 hipError_t enqueue_response(dmpt_batch* b, hipStream_t s) {
-  const int P = b->count;
-  hipLaunchKernelGGL(k_b_gersh, dim3(b->tb.size()), dim3(kBlk), 0, s, b->dp, b->dtb, b->h0tab,
-                     b->part_g);
-  hipLaunchKernelGGL(k_b_setup, dim3(P), dim3(kBlk), 0, s, b->dp, b->part_g, b->max_layers);
-  hipLaunchKernelGGL(k_b_maxabs1, dim3(b->c1.size()), dim3(kBlk), 0, s, b->dp, b->dc1, b->h1tab,
-                     b->part1m);
-  hipLaunchKernelGGL(k_b_s1setup, dim3(P), dim3(kBlk), 0, s, b->dp, b->part1m);
-  hipLaunchKernelGGL(k_b_init<T16>, dim3(b->c0.size()), dim3(kBlk), 0, s, b->dp, b->dc0, b->h0tab,
-                     b->h1tab, b->t);
-  hipLaunchKernelGGL(k_b_init<T16>, dim3(b->c1.size()), dim3(kBlk), 0, s, b->dp, b->dc1, b->h0tab,
-                     b->h1tab, b->t);
-  hipError_t e = hipGetLastError();
-  for (int n = 1; n <= b->max_layers && e == hipSuccess; ++n) {
+  const int P = b->n_layered;
+  hipError_t e = hipSuccess;
+  // The launches of the small problems beside each other (each is a chain of
+  // layers on as many CUs as it has problems: 0.15 to 0.9 ms for 400 to 900
+  // problems, 0.3 to 0.5 ms for a few), and all of them before the layered
+  // problems, whose launches want every CU.
+  const int nt = (int)b->tiny.size(), sides = std::min(nt - 1, kTinySides);
+  if (sides > 0) e = hipEventRecord(b->fork, s);
+  for (int i = 0; i < sides && e == hipSuccess; ++i) e = hipStreamWaitEvent(b->side[i], b->fork, 0);
+  for (int i = 0; i < nt && e == hipSuccess; ++i) {
+    const auto& t = b->tiny[i];
+    TinyArgs a;
+    memset(&a, 0, sizeof(a));
+    a.probs = b->dtiny + t.first;
+    a.h0tab = b->h0tab;
+    a.h1tab = b->h1tab;
+    a.max_layers = b->max_layers;
+    const int lane = i % (sides + 1);
+    e = launch_tiny(b->prec, t.nf, t.k, a, t.count, lane == 0 ? s : b->side[lane - 1]);
+  }
+  for (int i = 0; i < sides && e == hipSuccess; ++i) {
+    e = hipEventRecord(b->join[i], b->side[i]);
+    if (e == hipSuccess) e = hipStreamWaitEvent(s, b->join[i], 0);
+  }
+  if (e != hipSuccess) return e;
+  if (P > 0) {
+    hipLaunchKernelGGL(k_b_gersh, dim3(b->tb.size()), dim3(kBlk), 0, s, b->dp, b->dtb, b->h0tab,
+                       b->part_g);
+    hipLaunchKernelGGL(k_b_setup, dim3(P), dim3(kBlk), 0, s, b->dp, b->part_g, b->max_layers);
+    hipLaunchKernelGGL(k_b_maxabs1, dim3(b->c1.size()), dim3(kBlk), 0, s, b->dp, b->dc1, b->h1tab,
+                       b->part1m);
+    hipLaunchKernelGGL(k_b_s1setup, dim3(P), dim3(kBlk), 0, s, b->dp, b->part1m);
+    hipLaunchKernelGGL(k_b_init<T16>, dim3(b->c0.size()), dim3(kBlk), 0, s, b->dp, b->dc0,
+                       b->h0tab, b->h1tab, b->t);
+    hipLaunchKernelGGL(k_b_init<T16>, dim3(b->c1.size()), dim3(kBlk), 0, s, b->dp, b->dc1,
+                       b->h0tab, b->h1tab, b->t);
+    e = hipGetLastError();
+  }
+  for (int n = 1; P > 0 && n <= b->max_layers && e == hipSuccess; ++n) {
     e = launch_trace_diag(b->prec, b->desc, b->dtb, (int)b->tb.size(), b->part_tr, s);
     if (e != hipSuccess) break;
     hipLaunchKernelGGL(k_b_predecide, dim3(P), dim3(kBlk), 0, s, b->dp, b->part_tr);
@@ -620,7 +665,7 @@ hipError_t enqueue_response(dmpt_batch* b, hipStream_t s) {
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_b_out, dim3(b->ob.size()), dim3(kBlk), 0, s, b->dp, b->dob, b->p0tab,
                      b->p1tab);
-  hipLaunchKernelGGL(k_b_summary, dim3(P), dim3(kWave), 0, s, b->dp, b->dsum);
+  hipLaunchKernelGGL(k_b_summary, dim3(b->count), dim3(kWave), 0, s, b->dp, b->dsum);
   return hipGetLastError();
 }
 
@@ -636,7 +681,7 @@ hipError_t enqueue(dmpt_batch* b, hipStream_t s) {
 // any response; MFMA timing does not depend on the values.
 hipError_t autotune(dmpt_batch* b) {
   int maxnp = 0;
-  for (auto& p : b->hp) maxnp = std::max<int>(maxnp, (int)p.np);
+  for (int p = 0; p < b->n_layered; ++p) maxnp = std::max<int>(maxnp, (int)b->hp[p].np);
   std::vector<int> cand = {0};
   for (int th = 256; th <= maxnp; th += 256) cand.push_back(th);
   hipEvent_t e0, e1;
@@ -695,6 +740,7 @@ dmpt_status dmpt_batch_init(dmpt_batch** out, int32_t count, const int64_t* N, c
   }
   dmpt_batch* b = new dmpt_batch();
   b->count = count;
+  b->k.assign(k, k + count);
   b->prec = (dmpt_precision)opt.precision;
   b->t = b->prec == DMPT_SPLIT_FP16 ? kLoShiftF16 : kLoShiftBF16;
   b->max_layers = opt.max_layers;
@@ -713,21 +759,45 @@ dmpt_status dmpt_batch_init(dmpt_batch** out, int32_t count, const int64_t* N, c
   };
   // sizes, block tables, sub-allocation offsets
   b->hp.resize(count);
-  size_t f32 = 0, u16 = 0;
+  std::vector<int> order, first_h1(count);
   int h1 = 0;
   for (int p = 0; p < count; ++p) {
-    BatchProblem& q = b->hp[p];
+    first_h1[p] = h1;
+    h1 += k[p];
+    if (!tiny_blocks(N[p], k[p])) order.push_back(p);
+  }
+  b->n_layered = (int)order.size();
+  for (int p = 0; p < count; ++p)
+    if (tiny_blocks(N[p], k[p])) order.push_back(p);
+  auto config = [&](int p) { return 4 * tiny_blocks(N[p], k[p]) + k[p]; };
+  std::stable_sort(order.begin() + b->n_layered, order.end(),
+                   [&](int x, int y) { return config(x) > config(y); });   // longest first
+  size_t f32 = 0, u16 = 0;
+  for (int i = 0; i < count; ++i) {
+    const int p = order[i];
+    const bool layered = i < b->n_layered;
+    BatchProblem& q = b->hp[i];
     memset(&q, 0, sizeof(q));
     q.n = N[p];
-    q.np = (N[p] + 255) / 256 * 256;
+    q.np = layered ? (N[p] + 255) / 256 * 256 : 32 * tiny_blocks(N[p], k[p]);
     q.ld = q.np;
     q.nocc = (double)Nocc[p];
     q.k = k[p];
     q.h0_index = p;
-    q.h1_first = h1;
-    h1 += k[p];
+    q.h1_first = first_h1[p];
     const size_t m = (size_t)q.np * q.ld;
     f32 += m * (1 + 2 * q.k);                          // S, S1_j x 2
+    const int nob = (int)((q.n + kOutB - 1) / kOutB);
+    for (int j = -1; j < q.k; ++j)
+      for (int bi = 0; bi < nob; ++bi)
+        for (int bj = 0; bj < nob; ++bj) b->ob.push_back(OutBlock{i, j, bi, bj});
+    if (!layered) {
+      if (b->tiny.empty() || b->tiny.back().nf != tiny_blocks(N[p], k[p]) ||
+          b->tiny.back().k != k[p])
+        b->tiny.push_back({tiny_blocks(N[p], k[p]), k[p], i - b->n_layered, 0});
+      ++b->tiny.back().count;
+      continue;
+    }
     u16 += (size_t)q.np * q.np * 4 * (1 + q.k);        // hi, lo x 2 buffers of S and S1_j
     const int64_t vec = m / 4;
     const int nch = (int)((vec + kChunkVec - 1) / kChunkVec);
@@ -735,18 +805,14 @@ dmpt_status dmpt_batch_init(dmpt_batch** out, int32_t count, const int64_t* N, c
     q.u0_count = nch;
     q.tr_first = (int)b->tb.size();
     q.tr_count = (int)((q.n + 31) / 32);
-    for (int r = 0; r < q.tr_count; ++r) b->tb.push_back(TraceBlock{p, r});
-    const int nob = (int)((q.n + kOutB - 1) / kOutB);
-    for (int j = -1; j < q.k; ++j)
-      for (int bi = 0; bi < nob; ++bi)
-        for (int bj = 0; bj < nob; ++bj) b->ob.push_back(OutBlock{p, j, bi, bj});
+    for (int r = 0; r < q.tr_count; ++r) b->tb.push_back(TraceBlock{i, r});
     for (int c = 0; c < nch; ++c)
-      b->c0.push_back(Chunk{p, -1, (int64_t)c * kChunkVec, std::min<int64_t>(vec, (int64_t)(c + 1) * kChunkVec)});
+      b->c0.push_back(Chunk{i, -1, (int64_t)c * kChunkVec, std::min<int64_t>(vec, (int64_t)(c + 1) * kChunkVec)});
     for (int j = 0; j < q.k; ++j) {
       q.u1_first[j] = (int)b->c1.size();
       q.u1_count[j] = nch;
       for (int c = 0; c < nch; ++c)
-        b->c1.push_back(Chunk{p, j, (int64_t)c * kChunkVec, std::min<int64_t>(vec, (int64_t)(c + 1) * kChunkVec)});
+        b->c1.push_back(Chunk{i, j, (int64_t)c * kChunkVec, std::min<int64_t>(vec, (int64_t)(c + 1) * kChunkVec)});
     }
   }
   b->total_k = h1;
@@ -772,8 +838,10 @@ dmpt_status dmpt_batch_init(dmpt_batch** out, int32_t count, const int64_t* N, c
   get((void**)&b->part_g, sizeof(double) * 3 * b->tb.size());
   get((void**)&b->part1m, sizeof(double) * b->c1.size());
   get((void**)&b->desc, sizeof(ProblemDesc) * count);
+  get((void**)&b->dtiny, sizeof(TinyProblem) * (count - b->n_layered));
   size_t n_big = 0, n_small = 0;
-  for (auto& q : b->hp) {
+  for (int p = 0; p < b->n_layered; ++p) {
+    const BatchProblem& q = b->hp[p];
     const int Tb = (int)((q.n + 255) / 256), Ts = (int)((q.n + 127) / 128);
     n_big += (size_t)(1 + q.k) * Tb * (Tb + 1) / 2;
     n_small += (size_t)(1 + q.k) * Ts * (Ts + 1) / 2;
@@ -804,6 +872,7 @@ dmpt_status dmpt_batch_init(dmpt_batch** out, int32_t count, const int64_t* N, c
       q.s1buf[j][0] = fbase + fo; fo += m;
       q.s1buf[j][1] = fbase + fo; fo += m;
     }
+    if (p >= b->n_layered) continue;
     for (int par = 0; par < 2; ++par) {
       q.s_hi[par] = hbase + ho; ho += pm;
       q.s_lo[par] = hbase + ho; ho += pm;
@@ -814,22 +883,43 @@ dmpt_status dmpt_batch_init(dmpt_batch** out, int32_t count, const int64_t* N, c
     }
   }
   // the products never write outside each problem's k extent: start from zero
-  if (hipMemset(fbase, 0, f32 * 4) != hipSuccess || hipMemset(hbase, 0, u16 * 2) != hipSuccess ||
+  std::vector<TinyProblem> tp(count - b->n_layered);
+  for (size_t i = 0; i < tp.size(); ++i) {
+    const BatchProblem& q = b->hp[b->n_layered + i];
+    TinyProblem& t = tp[i];
+    memset(&t, 0, sizeof(t));
+    t.state = q.st;
+    t.s_master = q.s_master;
+    for (int j = 0; j < q.k; ++j)
+      for (int par = 0; par < 2; ++par) t.s1buf[j][par] = q.s1buf[j][par];
+    t.ld = q.ld;
+    t.nocc = q.nocc;
+    t.n = (int32_t)q.n;
+    t.h0 = q.h0_index;
+    t.h1 = q.h1_first;
+  }
+  auto put = [&](void* dst, const void* src, size_t bytes) {
+    return bytes == 0 || hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice) == hipSuccess;
+  };
+  if (hipMemset(fbase, 0, f32 * 4) != hipSuccess ||
+      (u16 > 0 && hipMemset(hbase, 0, u16 * 2) != hipSuccess) ||
       hipMemset(sbase, 0, sizeof(LayerState) * count) != hipSuccess ||
-      hipMemcpy(b->dc0, b->c0.data(), sizeof(Chunk) * b->c0.size(), hipMemcpyHostToDevice) !=
-          hipSuccess ||
-      hipMemcpy(b->dc1, b->c1.data(), sizeof(Chunk) * b->c1.size(), hipMemcpyHostToDevice) !=
-          hipSuccess ||
-      hipMemcpy(b->dtb, b->tb.data(), sizeof(TraceBlock) * b->tb.size(), hipMemcpyHostToDevice) !=
-          hipSuccess ||
-      hipMemcpy(b->dob, b->ob.data(), sizeof(OutBlock) * b->ob.size(), hipMemcpyHostToDevice) !=
-          hipSuccess)
+      !put(b->dc0, b->c0.data(), sizeof(Chunk) * b->c0.size()) ||
+      !put(b->dc1, b->c1.data(), sizeof(Chunk) * b->c1.size()) ||
+      !put(b->dtb, b->tb.data(), sizeof(TraceBlock) * b->tb.size()) ||
+      !put(b->dob, b->ob.data(), sizeof(OutBlock) * b->ob.size()) ||
+      !put(b->dtiny, tp.data(), sizeof(TinyProblem) * tp.size()))
     return bail(DMPT_EHIP, "workspace set-up failed");
   if (hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking) != hipSuccess ||
       hipEventCreate(&b->ev0) != hipSuccess || hipEventCreate(&b->ev1) != hipSuccess)
     return bail(DMPT_EHIP, "stream/event creation failed");
-  if (opt.tile_threshold >= 0) {
-    if (build_class_items(b, opt.tile_threshold) != hipSuccess)
+  for (int i = 0; i < std::min((int)b->tiny.size() - 1, kTinySides); ++i)
+    if (hipStreamCreateWithFlags(&b->side[i], hipStreamNonBlocking) != hipSuccess ||
+        hipEventCreateWithFlags(&b->join[i], hipEventDisableTiming) != hipSuccess ||
+        (!b->fork && hipEventCreateWithFlags(&b->fork, hipEventDisableTiming) != hipSuccess))
+      return bail(DMPT_EHIP, "stream/event creation failed");
+  if (opt.tile_threshold >= 0 || b->n_layered == 0) {
+    if (build_class_items(b, std::max(opt.tile_threshold, 0)) != hipSuccess)
       return bail(DMPT_EHIP, "tile item set-up failed");
   } else if (autotune(b) != hipSuccess) {
     return bail(DMPT_EHIP, "tile autotuning failed");
@@ -893,7 +983,7 @@ dmpt_status dmpt_batch_response(dmpt_batch* b, const double* const* H0, const do
       st[p].layers = q.layers;
       st[p].d0_layer = q.d0_layer;
       st[p].converged = q.converged;
-      st[p].k = b->hp[p].k;
+      st[p].k = b->k[p];
       for (int j = 0; j < kMaxKB; ++j) st[p].d1_layer[j] = q.d1_layer[j];
       st[p].idem0 = q.idem0;
       for (int j = 0; j < kMaxKB; ++j) st[p].idem1[j] = q.idem1[j];

@@ -46,6 +46,7 @@ __host__ __device__ __forceinline__ int64_t panel_index(int64_t r, int64_t c, in
 // needs no host round trip.  Written only by the single-workgroup decision
 // kernels; read by every kernel of the next steps.
 struct LayerState {
+  static constexpr int kHist = -1;   // index mask of the per-layer histories (all kept)
   // configuration
   int32_t n_real;            // N
   int32_t k;                 // number of responses
@@ -159,6 +160,28 @@ struct ProductArgs {
                              // operands are zero from N on, so every k past N adds exact zeros)
 };
 
+// A problem small enough for one workgroup (launch_tiny).
+struct TinyProblem {
+  LayerState* state;
+  const float* s_init;       // single problem: normalised S0, row stride ld
+  float* s_master;           // batch: FP32 masters, row stride ld (upper triangles written)
+  float* s1buf[kMaxKB][2];
+  int64_t ld;
+  double nocc;
+  int32_t n;
+  int32_t h0, h1;            // batch: positions in the input tables
+};
+struct TinyArgs {
+  const TinyProblem* probs;  // batch: one per workgroup; NULL: `one`, FP64 outputs p0, p1
+  TinyProblem one;
+  const double* const* h0tab;
+  const double* const* h1tab;
+  const double* h1[kMaxKB];
+  double* p0;
+  double* p1[kMaxKB];
+  int32_t max_layers;
+};
+
 // ----------------------------------------------------------------- launchers
 // layer products (kernels_gemm.hip)
 int product_tile(dmpt_precision prec);   // output tile edge used by the product kernels
@@ -195,6 +218,13 @@ hipError_t launch_products_pair(dmpt_precision prec, const ProductArgs& a, hipSt
 // the diagonal of block b (problems with D0 open).
 hipError_t launch_trace_diag(dmpt_precision prec, const ProblemDesc* probs,
                              const TraceBlock* blocks, int n_blocks, double* part, hipStream_t s);
+
+// Whole recursions of small problems, one workgroup each (kernels_tiny.hip).
+// tiny_blocks: 32-row blocks of such a problem, 0 if N or k is too large for
+// the LDS of one CU.  launch_tiny: `count` problems of the same nf and k.
+int tiny_blocks(int64_t n, int k);
+hipError_t launch_tiny(dmpt_precision prec, int nf, int k, const TinyArgs& a, int count,
+                       hipStream_t s);
 
 // layer kernels (kernels_layer.hip)
 hipError_t launch_gershgorin(const double* H, int64_t n, double* partial /* 3*512 */,

@@ -22,6 +22,7 @@
 #include <algorithm>
 
 #include "layer_common.h"
+#include "split_mfma.h"
 
 namespace dmpt {
 
@@ -49,28 +50,6 @@ template <typename T>
 __device__ __forceinline__ T* uni(T* p) { return (T*)uni((int64_t)p); }
 
 // ------------------------------------------------------------------ split form
-template <typename T16> struct Split16;
-
-template <> struct Split16<_Float16> {
-  typedef f16x8 V;
-  static constexpr int kShift = kLoShiftF16;
-  static __device__ __forceinline__ f32x16 mma(V a, V b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ V up(V a) {
-    return a * (_Float16)(float)(1 << kShift);
-  }
-};
-
-template <> struct Split16<__bf16> {
-  typedef bf16x8 V;
-  static constexpr int kShift = kLoShiftBF16;
-  static __device__ __forceinline__ f32x16 mma(V a, V b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ V up(V a) { return a; }  // t = 0
-};
-
 // Resolve the skip flags and the operand scale of one tile item.
 // Returns false when the item has nothing to do.  Plain launches run after
 // nothing was decided for the layer: X is skipped once D0 converged.  Fused
@@ -514,11 +493,8 @@ k_products_split(const ProductArgs a) {
   // waves in index order
   __shared__ double red_f[WGM * WGN];
   __shared__ float red_m[WGM * WGN];
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) {
-    pf += __shfl_xor(pf, o);
-    pm = fmaxf(pm, __shfl_xor(pm, o));
-  }
+  pf = wave_sum(pf);
+  pm = wave_max(pm);
   if (lane == 0) {
     red_f[wave] = pf;
     red_m[wave] = pm;
@@ -540,18 +516,6 @@ k_products_split(const ProductArgs a) {
 }
 
 // ------------------------------------------------------------------ batched pairs
-// Barrier for hand-offs through the LDS: this wave's LDS accesses have
-// completed and the compiler keeps memory accesses on their side of it.
-// Outstanding global stores and direct-to-LDS loads are not waited for (a
-// workgroup fence would wait for all of them); callers wait for their loads
-// explicitly.  Global memory written in a launch is not read back in it.
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(LgkWait<0>::imm);
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 // Memory that no kernel writes while the product launch runs (the items, the
 // problem descriptors, the layer states, which the decision kernels write
 // between launches), read through the constant address space: workgroup-
@@ -993,11 +957,8 @@ k_products_pair(const ProductArgs a) {
   // waves in index order
   __shared__ double red_f[WGM * WGN];
   __shared__ float red_m[WGM * WGN];
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) {
-    pf += __shfl_xor(pf, o);
-    pm = fmaxf(pm, __shfl_xor(pm, o));
-  }
+  pf = wave_sum(pf);
+  pm = wave_max(pm);
   if (lane == 0) {
     red_f[wave] = pf;
     red_m[wave] = pm;
@@ -1555,8 +1516,7 @@ __global__ void __launch_bounds__(kWave) k_trace_diag(const ProblemDesc* probs,
       if (r == ri) x = acc[r] * scale;
     v = (double)x;
   }
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  v = wave_sum(v);
   if (lane == 0) part[blockIdx.x] = v;
 }
 

@@ -11,20 +11,90 @@ namespace dmpt {
 constexpr int kBlk = 256;
 
 // ------------------------------------------------------------------ helpers
+// Reductions over a wave: lane l meets lane l ^ o for o = 32, 16, 8, 4, 2, 1.
+// The two halves (row pairs) are exchanged by permlane swaps.  After those
+// steps the values repeat every 2 o lanes, so a rotation by o within the rows
+// of 16 lanes brings the same partner: no LDS round trip per step.
+template <int O>
+static __device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+  static_assert(O == 8 || O == 4 || O == 2 || O == 1, "rotations within a row");
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + O, 0xf, 0xf, true);   // row_ror
+}
+template <int O>
+static __device__ __forceinline__ float lane_xor(float v) {
+  return __builtin_bit_cast(float, lane_xor<O>(__builtin_bit_cast(uint32_t, v)));
+}
+template <int O>
+static __device__ __forceinline__ double lane_xor(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  return __builtin_bit_cast(double, (uint64_t)lane_xor<O>((uint32_t)u) |
+                                        ((uint64_t)lane_xor<O>((uint32_t)(u >> 32)) << 32));
+}
+// a and b: v of the lower and of the upper half of every 2 O lanes (O = 32, 16)
+template <int O>
+static __device__ __forceinline__ void lane_halves(uint32_t v, uint32_t* a, uint32_t* b) {
+  static_assert(O == 32 || O == 16, "permlane swaps");
+  if constexpr (O == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    *a = r[0];
+    *b = r[1];
+  } else {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    *a = r[0];
+    *b = r[1];
+  }
+}
+template <int O>
+static __device__ __forceinline__ void lane_halves(float v, float* a, float* b) {
+  uint32_t x, y;
+  lane_halves<O>(__builtin_bit_cast(uint32_t, v), &x, &y);
+  *a = __builtin_bit_cast(float, x);
+  *b = __builtin_bit_cast(float, y);
+}
+template <int O>
+static __device__ __forceinline__ void lane_halves(double v, double* a, double* b) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  uint32_t x0, y0, x1, y1;
+  lane_halves<O>((uint32_t)u, &x0, &y0);
+  lane_halves<O>((uint32_t)(u >> 32), &x1, &y1);
+  *a = __builtin_bit_cast(double, (uint64_t)x0 | ((uint64_t)x1 << 32));
+  *b = __builtin_bit_cast(double, (uint64_t)y0 | ((uint64_t)y1 << 32));
+}
+template <typename T, typename F>
+static __device__ __forceinline__ T wave_reduce(T v, F op) {
+  T a, b;
+  lane_halves<32>(v, &a, &b);
+  v = op(a, b);
+  lane_halves<16>(v, &a, &b);
+  v = op(a, b);
+  v = op(v, lane_xor<8>(v));
+  v = op(v, lane_xor<4>(v));
+  v = op(v, lane_xor<2>(v));
+  return op(v, lane_xor<1>(v));
+}
 static __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
+  return wave_reduce(v, [](double x, double y) { return x + y; });
 }
 static __device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-  return v;
+  return wave_reduce(v, [](double x, double y) { return fmax(x, y); });
+}
+static __device__ __forceinline__ float wave_max(float v) {
+  return wave_reduce(v, [](float x, float y) { return fmaxf(x, y); });
 }
 static __device__ __forceinline__ double wave_min(double v) {
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o));
-  return v;
+  return wave_reduce(v, [](double x, double y) { return fmin(x, y); });
+}
+
+// Barrier for hand-offs through the LDS: this wave's LDS accesses have
+// completed and the compiler keeps memory accesses on their side of it.
+// Outstanding global stores and direct-to-LDS loads are not waited for (a
+// workgroup fence would wait for all of them); callers wait for their loads
+// explicitly and read no global memory that another wave wrote.
+static __device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0), the others free
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
 // Block-wide reductions for kBlk threads; the result is valid in every thread.
@@ -96,7 +166,11 @@ static __device__ __forceinline__ void split_one(float v, int e, int t, uint16_t
 // Algorithm 1 trace test and Algorithm 2 for layer n = st->n + 1, given
 // N_X = Tr X_n (thread 0 only): IdErr, sigma, the D0 test and the N_S update.
 // After D0 converged: sigma flips.
-static __device__ void decide0_apply(LayerState* st, double nx) {
+// St: LayerState, or a workgroup's own copy with the same fields and the last
+// kHist + 1 entries of the per-layer histories.
+template <typename St>
+static __device__ __forceinline__ void decide0_apply(St* st, double nx) {
+  constexpr int H = St::kHist;                 // history index mask
   const int d0 = st->d0;
   const int n = st->n + 1;
   st->n = n;
@@ -112,16 +186,16 @@ static __device__ void decide0_apply(LayerState* st, double nx) {
     const double iderr = ns - nx;
     const double a = fabs(2.0 * ns - nx - nocc), b = fabs(nx - nocc);
     sig = a > b ? 1 : -1;
-    st->iderr[n] = iderr;
+    st->iderr[n & H] = iderr;
     const bool conv = iderr <= 0.0 ||
-                      (n > 2 && st->sigma[n - 1] != st->sigma[n - 2] &&
-                       iderr > 4.5 * st->iderr[n - 2] * st->iderr[n - 2]);
+                      (n > 2 && st->sigma[(n - 1) & H] != st->sigma[(n - 2) & H] &&
+                       iderr > 4.5 * st->iderr[(n - 2) & H] * st->iderr[(n - 2) & H]);
     if (conv) {
       st->d0 = 1;
       st->d0_layer = n;
       st->d0_now = 1;
       st->upd_s0 = 0;
-      if (n > 1) sig = -st->sigma[n - 1];
+      if (n > 1) sig = -st->sigma[(n - 1) & H];
     } else {
       st->d0_now = 0;
       st->upd_s0 = 1;
@@ -131,9 +205,9 @@ static __device__ void decide0_apply(LayerState* st, double nx) {
     st->x_computed = 0;
     st->upd_s0 = 0;
     st->d0_now = 0;
-    sig = -st->sigma[n - 1];
+    sig = -st->sigma[(n - 1) & H];
   }
-  st->sigma[n] = sig;
+  st->sigma[n & H] = sig;
   st->sigma_cur = sig;
 }
 
@@ -247,9 +321,12 @@ struct Partials {
 // two layers after the D1 layer of the first perturbation: with S0 and S1
 // frozen its map has the same linear part as the first-order map.  f0sq = ||S - X||_F^2
 // (used at the D0 layer), f1sq[j] = ||S1_j - X1_j||_F^2, m1[j] = max|S1_j,n|.
-static __device__ void decide1_apply(LayerState* st, double f0sq, const double* f1sq,
+// KC > 0: the number of responses, known at compile time.
+template <int KC = 0, typename St>
+static __device__ __forceinline__ void decide1_apply(St* st, double f0sq, const double* f1sq,
                                      const double* m1, int split, int lo_shift) {
-  const int k = st->k;
+  constexpr int H = St::kHist;
+  const int k = KC > 0 ? KC : st->k;
   const int d0 = st->d0;
   const int n = st->n;
   if (st->d0_now) {
@@ -257,6 +334,7 @@ static __device__ void decide1_apply(LayerState* st, double f0sq, const double* 
     if (!isfinite(st->fro0)) st->error = DMPT_ENONFINITE;
   }
   int all = 1;
+#pragma unroll(KC > 0 ? KC : 1)
   for (int j = 0; j < k; ++j) {
     if (st->d1[j]) continue;
     const double mx = m1[j];
@@ -265,21 +343,21 @@ static __device__ void decide1_apply(LayerState* st, double f0sq, const double* 
     if (!isfinite(mx)) st->error = DMPT_ENONFINITE;
     if (d0) {
       const double f = sqrt(f1sq[j]);
-      st->fro1[j][n] = f;
+      st->fro1[j][n & H] = f;
       if (!isfinite(f)) st->error = DMPT_ENONFINITE;
       // first order: two layers after D0; the second-order chain: two layers
       // after the D1 layer of the first perturbation (S0 and S1 frozen)
       const bool armed = j == st->order2_slot ? (st->d1[0] && n - 2 >= st->d1_layer[0])
                                               : n - 2 >= st->d0_layer;
       if (armed) {
-        const double prev = st->fro1[j][n - 2];
+        const double prev = st->fro1[j][(n - 2) & H];
         if (f > 9.0 * st->fro0 * prev || f == 0.0) {
           st->d1[j] = 1;
           st->d1_layer[j] = n;
         }
       }
     }
-    st->s1_exp_hist[j][n] = st->s1_exp_next[j];   // the scale S1_n was just split with
+    st->s1_exp_hist[j][n & H] = st->s1_exp_next[j];   // the scale S1_n was just split with
     st->s1_exp_split[j] = st->s1_exp_next[j];
     st->s1_exp_next[j] = split_exponent(mx);
     st->s1_max[j] = mx;
