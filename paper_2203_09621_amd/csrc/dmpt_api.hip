@@ -230,7 +230,6 @@ struct dmpt_ctx {
   int n_items[kMaxK + 1];
   LayerState* hstate; // pinned host copy
   int32_t* hflag;     // pinned host flag
-  double* hscal;      // pinned host scalars
   hipEvent_t ev0, ev1;
   int timing;
   hipEvent_t pev[2 * kMaxLayers];  // per-layer product launch bracket (timing on)
@@ -259,7 +258,7 @@ constexpr size_t kPartFro1 = kRedBlocks;
 constexpr size_t kPartMax1 = kPartFro1 + (size_t)kMaxK * kRedBlocks;
 constexpr size_t kPartGersh = kPartMax1 + (size_t)kMaxK * kRedBlocks;
 constexpr size_t kPartMaxabs = kPartGersh + 3 * 512;
-constexpr size_t kPartTotal = kPartMaxabs + kRedBlocks;
+constexpr size_t kPartTotal = kPartMaxabs + (size_t)kMaxK * kRedBlocks;
 
 void ctx_free(dmpt_ctx* c) {
   if (!c) return;
@@ -267,7 +266,6 @@ void ctx_free(dmpt_ctx* c) {
   c->mem.release();
   if (c->hstate) (void)hipHostFree(c->hstate);
   if (c->hflag) (void)hipHostFree(c->hflag);
-  if (c->hscal) (void)hipHostFree(c->hscal);
   if (c->ev0) (void)hipEventDestroy(c->ev0);
   if (c->ev1) (void)hipEventDestroy(c->ev1);
   for (int i = 0; i < 2 * kMaxLayers; ++i)
@@ -295,12 +293,11 @@ dmpt_status normalise(dmpt_ctx* c, const double* H0) {
   }
   hipStream_t s = c->stream;
   c->last_k = 0;   // checkpoints and decisions of an earlier response no longer apply
-  HIPCHK(hipMemsetAsync(c->st, 0, sizeof(LayerState), s));
   HIPCHK(launch_gershgorin(H0, c->n, c->part + kPartGersh, c->st, c->dscal, s));
   HIPCHK(launch_init_s0(c->prec, H0, c->n, c->np, c->ld, c->st, c->s_init, s));
-  HIPCHK(hipMemcpyAsync(c->hstate, c->st, sizeof(LayerState), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(c->hflag, &c->st->error, sizeof(int32_t), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
-  if (c->hstate->error) return fail((dmpt_status)c->hstate->error, "non-finite Gershgorin bounds");
+  if (c->hflag[0]) return fail((dmpt_status)c->hflag[0], "non-finite Gershgorin bounds");
   return DMPT_OK;
 }
 
@@ -504,6 +501,7 @@ dmpt_status dmpt_init(dmpt_ctx** out, const double* H0, int64_t N, int64_t Nocc,
   if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation)
     return bail(DMPT_ENOMEM, "device allocation failed");
   // the products never write the pad columns of X and X1: they must start at zero
+  if (e == hipSuccess) e = hipMemset(c->st, 0, sizeof(LayerState));
   if (e == hipSuccess && c->x) e = hipMemset(c->x, 0, mat * eb);
   for (int j = 0; j < k_max && e == hipSuccess; ++j) {
     e = hipMemset(c->s1buf[j][0], 0, mat * eb);
@@ -511,8 +509,7 @@ dmpt_status dmpt_init(dmpt_ctx** out, const double* H0, int64_t N, int64_t Nocc,
   }
   if (e != hipSuccess) return bail(DMPT_EHIP, std::string("allocation: ") + hipGetErrorString(e));
   if (hipHostMalloc((void**)&c->hstate, sizeof(LayerState), 0) != hipSuccess ||
-      hipHostMalloc((void**)&c->hflag, 16 * sizeof(int32_t), 0) != hipSuccess ||
-      hipHostMalloc((void**)&c->hscal, 16 * sizeof(double), 0) != hipSuccess)
+      hipHostMalloc((void**)&c->hflag, 16 * sizeof(int32_t), 0) != hipSuccess)
     return bail(DMPT_ENOMEM, "pinned host allocation failed");
   if (hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess)
     return bail(DMPT_EHIP, "event creation failed");
@@ -546,10 +543,11 @@ template <typename Out>
 dmpt_status finish_response(dmpt_ctx* c, int k, bool order2, double* P0, Out slot_out, int n,
                             dmpt_stats* stats) {
   hipStream_t s = c->stream;
-  if (P0) HIPCHK(launch_trace(P0, c->n, c->dscal, s));
-  for (int j = 0; j < k; ++j) HIPCHK(launch_trace(slot_out(j), c->n, c->dscal + 1 + j, s));
+  MatList out;
+  out.p[0] = P0;
+  for (int j = 0; j < k; ++j) out.p[1 + j] = slot_out(j);
+  HIPCHK(launch_traces(out, 1 + k, c->n, c->st, s));
   HIPCHK(hipMemcpyAsync(c->hstate, c->st, sizeof(LayerState), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(c->hscal, c->dscal, 16 * sizeof(double), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   const LayerState& h = *c->hstate;
   if (stats) {
@@ -563,11 +561,11 @@ dmpt_status finish_response(dmpt_ctx* c, int k, bool order2, double* P0, Out slo
     stats->epsN = h.epsN;
     stats->n_s = h.n_s;
     stats->idem0 = h.fro0;
-    stats->trace_p0 = P0 ? c->hscal[0] : 0.0;
+    stats->trace_p0 = h.traces[0];
     for (int j = 0; j < k; ++j) {
       stats->d1_layer[j] = h.d1_layer[j];
       stats->idem1[j] = h.d1_layer[j] > 0 ? h.fro1[j][h.d1_layer[j]] : 0.0;
-      stats->trace_p1[j] = c->hscal[1 + j];
+      stats->trace_p1[j] = h.traces[1 + j];
     }
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, c->ev0, c->ev1) != hipSuccess) ms = 0.f;
@@ -641,9 +639,16 @@ dmpt_status run_response(dmpt_ctx* c, const double* const* H1, int k1, bool orde
   }
   HIPCHK(launch_reset_state(c->st, k, order2 ? k1 : -1, c->max_layers, (double)c->nocc, c->n, s));
   HIPCHK(launch_load_s0(prec, c->s_init, c->s_master, c->s_hi[0], c->s_lo[0], np, ld, t, s));
-  for (int j = 0; j < k; ++j)
-    HIPCHK(launch_init_s1(prec, slot_in(j), c->n, np, ld, c->st, j, c->part + kPartMaxabs,
-                          c->s1buf[j][0], c->s1_hi[j][0], c->s1_lo[j][0], t, 0.0, s));
+  MatList h1, s1[2], hi, lo;
+  for (int j = 0; j < k; ++j) {
+    h1.p[j] = (void*)slot_in(j);
+    s1[0].p[j] = c->s1buf[j][0];
+    s1[1].p[j] = c->s1buf[j][1];
+    hi.p[j] = c->s1_hi[j][0];
+    lo.p[j] = c->s1_lo[j][0];
+  }
+  HIPCHK(launch_init_s1(prec, h1, k, c->n, np, ld, c->st, c->part + kPartMaxabs, s1[0], hi, lo, t,
+                        s));
 
   const size_t mbytes = (size_t)elems * elem_bytes(prec);
   auto save_ckpt = [&](int layer) -> hipError_t {
@@ -719,10 +724,11 @@ dmpt_status run_response(dmpt_ctx* c, const double* const* H1, int k1, bool orde
       stopped = c->hflag[0] != 0;
     }
   }
-  if (P0) HIPCHK(launch_copy_out(prec, c->st, -1, c->s_master, c->s_master, ld, P0, c->n, s));
-  for (int j = 0; j < k; ++j)
-    HIPCHK(launch_copy_out(prec, c->st, j, c->s1buf[j][0], c->s1buf[j][1], ld, slot_out(j), c->n,
-                           s));
+  MatList out;
+  out.p[0] = P0;
+  for (int j = 0; j < k; ++j) out.p[1 + j] = slot_out(j);
+  HIPCHK(launch_copy_out(prec, c->st, P0 ? 0 : 1, P0 ? 1 + k : k, c->s_master, s1[0], s1[1], ld,
+                         out, c->n, s));
   HIPCHK(hipEventRecord(c->ev1, s));
   return finish_response(c, k, order2, P0, slot_out, n, stats);
 }
@@ -1174,11 +1180,7 @@ dmpt_status dmpt_contract(const double* const* A, int32_t na, const double* cons
     (void)hipFree(part);
     return fail(DMPT_ENOMEM, "allocation failed");
   }
-  hipError_t e = hipSuccess;
-  for (int a = 0; a < na && e == hipSuccess; ++a)
-    for (int b = 0; b < nb && e == hipSuccess; ++b)
-      e = launch_contract(A[a], B[b], N, part + (size_t)(a * nb + b) * kRedBlocks,
-                          dev + a * nb + b, s);
+  hipError_t e = launch_contract(A, na, B, nb, N, part, dev, s);
   if (e == hipSuccess)
     e = hipMemcpyAsync(out, dev, (size_t)np * sizeof(double), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -1244,11 +1246,7 @@ dmpt_status dmpt_contract_noalloc(const double* const* A, int32_t na, const doub
   double* dev = base + (size_t)kNoAllocPairs * kRedBlocks;
   hipStream_t s = (hipStream_t)stream;
   const int np = na * nb;
-  hipError_t e = hipSuccess;
-  for (int a = 0; a < na && e == hipSuccess; ++a)
-    for (int b = 0; b < nb && e == hipSuccess; ++b)
-      e = launch_contract(A[a], B[b], N, part + (size_t)(a * nb + b) * kRedBlocks,
-                          dev + a * nb + b, s);
+  hipError_t e = launch_contract(A, na, B, nb, N, part, dev, s);
   if (e == hipSuccess)
     e = hipMemcpyAsync(out, dev, (size_t)np * sizeof(double), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);

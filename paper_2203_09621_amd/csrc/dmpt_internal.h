@@ -81,6 +81,12 @@ struct LayerState {
   double fro1[kMaxK][kMaxLayers + 1];
   double s1_max[kMaxK];
   int32_t s1_exp_hist[kMaxK][kMaxLayers + 1];   // split scale S1_n was written with
+  double traces[1 + kMaxK];        // Tr P0 and Tr P1_j of the last response's outputs
+};
+
+// Matrices of a launch that covers several of them (S and every response).
+struct MatList {
+  void* p[1 + kMaxK] = {};
 };
 
 // One output tile of a layer product.  out = 0: X = S^2; out = 1 + j: X1_j,
@@ -237,9 +243,11 @@ hipError_t launch_init_s0(dmpt_precision prec, const double* H0, int64_t n, int6
                           int64_t ld, const LayerState* st, void* s_init, hipStream_t s);
 hipError_t launch_load_s0(dmpt_precision prec, const void* s_init, void* master, void* hi, void* lo,
                           int64_t rows, int64_t ld, int t, hipStream_t s);
-hipError_t launch_init_s1(dmpt_precision prec, const double* H1, int64_t n, int64_t rows,
-                          int64_t ld, LayerState* st, int j, double* partial, void* s1, void* hi,
-                          void* lo, int t, double w_fixed, hipStream_t s);
+// S1_0 of responses 0 .. k-1 (H1.p[j] NULL: zero) with their split scales;
+// part: k kRedBlocks FP64 partials.
+hipError_t launch_init_s1(dmpt_precision prec, const MatList& H1, int k, int64_t n, int64_t rows,
+                          int64_t ld, LayerState* st, double* part, const MatList& s1,
+                          const MatList& hi, const MatList& lo, int t, hipStream_t s);
 // k response slots; order2_slot (-1: none) carries the second-order chain.
 hipError_t launch_reset_state(LayerState* st, int k, int order2_slot, int max_layers, double nocc,
                               int64_t n, hipStream_t s);
@@ -256,18 +264,21 @@ hipError_t launch_predecide(LayerState* st, const double* part, int np, hipStrea
 hipError_t launch_postdecide(LayerState* st, const TileItem* items, int n_items,
                              const double* part_f, const double* part_m, int lo_shift,
                              hipStream_t s);
-hipError_t launch_copy_out(dmpt_precision prec, const LayerState* st, int which, const void* b0,
-                           const void* b1, int64_t ld, double* dst, int64_t n, hipStream_t s);
-hipError_t launch_trace(const double* P, int64_t n, double* out, hipStream_t s);
+// Outputs first .. first + count - 1 (0: S from s0; 1 + j: response j from its
+// buffer b0.p[j] or b1.p[j]) into dst.p[output].
+hipError_t launch_copy_out(dmpt_precision prec, const LayerState* st, int first, int count,
+                           const void* s0, const MatList& b0, const MatList& b1, int64_t ld,
+                           const MatList& dst, int64_t n, hipStream_t s);
+hipError_t launch_traces(const MatList& P, int count, int64_t n, LayerState* st, hipStream_t s);
 // self-consistent response: heff = (1 - mix) heff + mix (h1 + g); out[0] = ||a - b||^2,
 // out[1] = ||a||^2 (part: 2 kRedBlocks FP64 partials)
 hipError_t launch_mix(const double* h1, const double* g, double* heff, double mix, int64_t n,
                       hipStream_t s);
 hipError_t launch_diff_norms(const double* a, const double* b, int64_t n, double* part,
                              double* out, hipStream_t s);
-// out = Tr(A B) for symmetric B (part: kRedBlocks FP64 partials)
-hipError_t launch_contract(const double* A, const double* B, int64_t n, double* part, double* out,
-                           hipStream_t s);
+// out[a nb + b] = Tr(A_a B_b) for symmetric B (part: na nb kRedBlocks FP64 partials)
+hipError_t launch_contract(const double* const* A, int na, const double* const* B, int nb,
+                           int64_t n, double* part, double* out, hipStream_t s);
 hipError_t launch_from_f64(dmpt_precision prec, const double* A, int64_t n, int64_t rows,
                            int64_t ld, int e, int t, void* master, void* hi, void* lo,
                            hipStream_t s);

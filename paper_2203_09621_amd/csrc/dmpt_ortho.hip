@@ -62,11 +62,9 @@ __global__ void __launch_bounds__(kBlk) k_dev_identity(const M* x, int64_t n, in
   if (threadIdx.x == 0) part[blockIdx.x] = v;
 }
 
-__global__ void k_sum_partials(const double* part, int nb, double* out) {
-  if (threadIdx.x != 0) return;
-  double v = 0.0;
-  for (int i = 0; i < nb; ++i) v += part[i];
-  *out = v;
+__global__ void __launch_bounds__(kBlk) k_sum_partials(const double* part, int nb, double* out) {
+  const double v = serial_sum(part, nb);
+  if (threadIdx.x == 0) *out = v;
 }
 
 dmpt_status ofail(dmpt_status s, const std::string& m) {
@@ -201,7 +199,7 @@ dmpt_status dmpt_inverse_factor(int32_t precision, const double* O, int64_t N, d
     else
       hipLaunchKernelGGL(k_dev_identity<float>, dim3(512), dim3(kBlk), 0, s, (const float*)x, N,
                          w.ld, w.part);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kWave), 0, s, w.part, 512, w.dscal);
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kBlk), 0, s, w.part, 512, w.dscal);
     double r2 = 0.0;
     e = hipMemcpyAsync(&r2, w.dscal, sizeof(double), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);

@@ -40,7 +40,7 @@ __global__ void __launch_bounds__(kBlk) k_gersh_rows(const double* H, int64_t n,
 // eps_1, eps_N, and N_S = Tr S0 = (N eps_N - Tr H0)/(eps_N - eps_1) into the state.
 __global__ void __launch_bounds__(kBlk) k_gersh_final(const double* part, int nb, int64_t n,
                                                      LayerState* st, double* eps_out) {
-  double lo = INFINITY, hi = -INFINITY, tr = 0.0;
+  double lo = INFINITY, hi = -INFINITY;
   for (int i = threadIdx.x; i < nb; i += kBlk) {
     lo = fmin(lo, part[i]);
     hi = fmax(hi, part[nb + i]);
@@ -48,15 +48,15 @@ __global__ void __launch_bounds__(kBlk) k_gersh_final(const double* part, int nb
   // the trace partials are combined in block order by one thread (fixed order)
   lo = block_min(lo);
   hi = block_max(hi);
+  const double tr = serial_sum(part + 2 * nb, nb);
   if (threadIdx.x == 0) {
-    for (int i = 0; i < nb; ++i) tr += part[2 * nb + i];
     if (eps_out) { eps_out[0] = lo; eps_out[1] = hi; }
     if (st) {
       st->eps1 = lo;
       st->epsN = hi;
       const double w = hi - lo;
       st->n_s0 = ((double)n * hi - tr) / w;
-      if (!(w > 0.0) || !isfinite(w)) st->error = DMPT_ENONFINITE;
+      st->error = w > 0.0 && isfinite(w) ? 0 : DMPT_ENONFINITE;
     }
   }
 }
@@ -86,19 +86,24 @@ hipError_t launch_symcheck(const double* H, int64_t n, int32_t* flag, hipStream_
   return hipGetLastError();
 }
 
-__global__ void __launch_bounds__(kBlk) k_maxabs(const double* H, int64_t total, double* part) {
+// max |H_j| partials, matrix j = blockIdx.y (a NULL matrix counts as zero)
+__global__ void __launch_bounds__(kBlk) k_maxabs(const MatList H, int64_t total, double* part) {
+  const double* h = (const double*)H.p[blockIdx.y];
   double m = 0.0;
-  for (int64_t q = (int64_t)blockIdx.x * kBlk + threadIdx.x; q < total;
-       q += (int64_t)gridDim.x * kBlk) {
-    const double v = fabs(H[q]);
-    m = (v > m || v != v) ? v : m;   // keeps a NaN
-  }
+  if (h)
+    for (int64_t q = (int64_t)blockIdx.x * kBlk + threadIdx.x; q < total;
+         q += (int64_t)gridDim.x * kBlk) {
+      const double v = fabs(h[q]);
+      m = (v > m || v != v) ? v : m;   // keeps a NaN
+    }
   m = block_max(m);
-  if (threadIdx.x == 0) part[blockIdx.x] = m;
+  if (threadIdx.x == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = m;
 }
 
 hipError_t launch_maxabs(const double* H, int64_t n, double* part, hipStream_t s) {
-  hipLaunchKernelGGL(k_maxabs, dim3(kRedBlocks), dim3(kBlk), 0, s, H, n * n, part);
+  MatList m;
+  m.p[0] = (void*)H;
+  hipLaunchKernelGGL(k_maxabs, dim3(kRedBlocks, 1), dim3(kBlk), 0, s, m, n * n, part);
   return hipGetLastError();
 }
 
@@ -180,14 +185,15 @@ hipError_t launch_load_s0(dmpt_precision prec, const void* s_init, void* master,
 
 // First-order input layer S1_0 = -H1/(eps_N - eps_1) (Sec. III.A expansion of
 // the normalisation).  Step 1: split scale from max|H1|.
-__global__ void __launch_bounds__(kBlk) k_s1_setup(const double* part, int nb, LayerState* st,
-                                                  int j, int use_state_eps, double w_fixed) {
+// Response j = blockIdx.x.
+__global__ void __launch_bounds__(kBlk) k_s1_setup(const double* part, int nb, LayerState* st) {
+  const int j = blockIdx.x;
+  part += (size_t)j * nb;
   double m = 0.0;
   for (int i = threadIdx.x; i < nb; i += kBlk) m = (part[i] > m || part[i] != part[i]) ? part[i] : m;
   m = block_max(m);
   if (threadIdx.x == 0) {
-    const double w = use_state_eps ? st->epsN - st->eps1 : w_fixed;
-    const double mx = m / w;
+    const double mx = m / (st->epsN - st->eps1);
     if (!isfinite(mx)) st->error = DMPT_ENONFINITE;
     const int e = split_exponent(mx);
     st->s1_exp_split[j] = e;
@@ -198,12 +204,18 @@ __global__ void __launch_bounds__(kBlk) k_s1_setup(const double* part, int nb, L
 }
 
 // Step 2: S1_0 (padded) in the layer precision, split with the state's scale.
+// Response j = blockIdx.y.
 template <typename M, typename T16, bool SPLIT>
-__global__ void __launch_bounds__(kBlk) k_init_s1(const double* H1, int64_t n, int64_t rows,
-                                                 int64_t ld, const LayerState* st, int j,
-                                                 double w_fixed, int use_state_eps, M* s1,
-                                                 uint16_t* hi, uint16_t* lo, int t) {
-  const double w = use_state_eps ? st->epsN - st->eps1 : w_fixed;
+__global__ void __launch_bounds__(kBlk) k_init_s1(const MatList H1s, int64_t n, int64_t rows,
+                                                 int64_t ld, const LayerState* st,
+                                                 const MatList s1s, const MatList his,
+                                                 const MatList los, int t) {
+  const int j = blockIdx.y;
+  const double* H1 = (const double*)H1s.p[j];   // NULL: a zero perturbation
+  M* s1 = (M*)s1s.p[j];
+  uint16_t* hi = (uint16_t*)his.p[j];
+  uint16_t* lo = (uint16_t*)los.p[j];
+  const double w = st->epsN - st->eps1;
   const int e = st->s1_exp_split[j];
   const int64_t total = rows * ld;
   for (int64_t q = (int64_t)blockIdx.x * kBlk + threadIdx.x; q < total;
@@ -222,39 +234,45 @@ __global__ void __launch_bounds__(kBlk) k_init_s1(const double* H1, int64_t n, i
   }
 }
 
-hipError_t launch_init_s1(dmpt_precision prec, const double* H1, int64_t n, int64_t rows,
-                          int64_t ld, LayerState* st, int j, double* part, void* s1, void* hi,
-                          void* lo, int t, double w_fixed, hipStream_t s) {
-  const int use_state = w_fixed > 0.0 ? 0 : 1;
-  // H1 == NULL: a zero perturbation (the second-order chain without H2)
-  hipLaunchKernelGGL(k_maxabs, dim3(kRedBlocks), dim3(kBlk), 0, s, H1, H1 ? n * n : 0, part);
-  hipLaunchKernelGGL(k_s1_setup, dim3(1), dim3(kBlk), 0, s, part, kRedBlocks, st, j, use_state,
-                     w_fixed);
+hipError_t launch_init_s1(dmpt_precision prec, const MatList& H1, int k, int64_t n, int64_t rows,
+                          int64_t ld, LayerState* st, double* part, const MatList& s1,
+                          const MatList& hi, const MatList& lo, int t, hipStream_t s) {
+  hipLaunchKernelGGL(k_maxabs, dim3(kRedBlocks, k), dim3(kBlk), 0, s, H1, n * n, part);
+  hipLaunchKernelGGL(k_s1_setup, dim3(k), dim3(kBlk), 0, s, part, kRedBlocks, st);
+  const dim3 grid(4096, k);
   switch (prec) {
     case DMPT_FP64:
-      hipLaunchKernelGGL((k_init_s1<double, _Float16, false>), dim3(4096), dim3(kBlk), 0, s, H1, n,
-                         rows, ld, st, j, w_fixed, use_state, (double*)s1, nullptr, nullptr, t);
+      hipLaunchKernelGGL((k_init_s1<double, _Float16, false>), grid, dim3(kBlk), 0, s, H1, n, rows,
+                         ld, st, s1, hi, lo, t);
       break;
     case DMPT_FP32:
-      hipLaunchKernelGGL((k_init_s1<float, _Float16, false>), dim3(4096), dim3(kBlk), 0, s, H1, n,
-                         rows, ld, st, j, w_fixed, use_state, (float*)s1, nullptr, nullptr, t);
+      hipLaunchKernelGGL((k_init_s1<float, _Float16, false>), grid, dim3(kBlk), 0, s, H1, n, rows,
+                         ld, st, s1, hi, lo, t);
       break;
     case DMPT_SPLIT_FP16:
-      hipLaunchKernelGGL((k_init_s1<float, _Float16, true>), dim3(4096), dim3(kBlk), 0, s, H1, n,
-                         rows, ld, st, j, w_fixed, use_state, (float*)s1, (uint16_t*)hi, (uint16_t*)lo, t);
+      hipLaunchKernelGGL((k_init_s1<float, _Float16, true>), grid, dim3(kBlk), 0, s, H1, n, rows,
+                         ld, st, s1, hi, lo, t);
       break;
     case DMPT_SPLIT_BF16:
-      hipLaunchKernelGGL((k_init_s1<float, __bf16, true>), dim3(4096), dim3(kBlk), 0, s, H1, n, rows, ld,
-                         st, j, w_fixed, use_state, (float*)s1, (uint16_t*)hi, (uint16_t*)lo, t);
+      hipLaunchKernelGGL((k_init_s1<float, __bf16, true>), grid, dim3(kBlk), 0, s, H1, n, rows, ld,
+                         st, s1, hi, lo, t);
       break;
   }
   return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ state reset
-__global__ void k_reset_state(LayerState* st, int k, int order2_slot, int max_layers, double nocc,
+__global__ void __launch_bounds__(kBlk) k_reset_state(LayerState* st, int k, int order2_slot, int max_layers, double nocc,
                               int64_t n) {
-  // one thread: a few hundred words
+  for (int i = threadIdx.x; i <= kMaxLayers; i += kBlk) {
+    st->sigma[i] = 0;
+    st->iderr[i] = 0.0;
+    for (int j = 0; j < kMaxK; ++j) st->fro1[j][i] = 0.0;
+  }
+  if (threadIdx.x < kMaxK) {
+    st->d1[threadIdx.x] = (int)threadIdx.x < k ? 0 : 1;
+    st->d1_layer[threadIdx.x] = 0;
+  }
   if (threadIdx.x != 0) return;
   st->n_real = (int32_t)n;
   st->k = k;
@@ -274,20 +292,11 @@ __global__ void k_reset_state(LayerState* st, int k, int order2_slot, int max_la
   st->s_par = 0;
   st->n_s = st->n_s0;
   st->fro0 = 0.0;
-  for (int i = 0; i <= kMaxLayers; ++i) {
-    st->sigma[i] = 0;
-    st->iderr[i] = 0.0;
-  }
-  for (int j = 0; j < kMaxK; ++j) {
-    st->d1[j] = j < k ? 0 : 1;
-    st->d1_layer[j] = 0;
-    for (int i = 0; i <= kMaxLayers; ++i) st->fro1[j][i] = 0.0;
-  }
 }
 
 hipError_t launch_reset_state(LayerState* st, int k, int order2_slot, int max_layers, double nocc,
                               int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(k_reset_state, dim3(1), dim3(kWave), 0, s, st, k, order2_slot, max_layers,
+  hipLaunchKernelGGL(k_reset_state, dim3(1), dim3(kBlk), 0, s, st, k, order2_slot, max_layers,
                      nocc, n);
   return hipGetLastError();
 }
@@ -380,34 +389,93 @@ hipError_t launch_decide1(LayerState* st, const double* pfro0, const double* pfr
 }
 
 // ------------------------------------------------------------------ observables
-// Tr(A B) for symmetric B as sum_ij A_ij B_ij: FP64 partial per block in a
-// fixed grid; the final sum runs in block order.
-__global__ void __launch_bounds__(kBlk) k_contract(const double* A, const double* B, int64_t total,
+// Tr(A_a B_b) for symmetric B as sum_ij A_ij B_ij: FP64 partials per block in a
+// fixed grid, then a fixed tree.  One launch covers up to kConA x kConB pairs:
+// it reads every matrix once for all of them, where a launch per pair reads
+// each one as often as it has partners (3 x 3 pairs at N = 4096: 18 matrices
+// of 134 MB, 44 us per pair, against 6), and its sums end in LDS instead of
+// one thread's chain of 1024 loads (55 us per pair).  Bound by the reads.
+constexpr int kConA = 3, kConB = 3;
+struct ConMats {
+  const double* a[kConA];
+  const double* b[kConB];
+};
+template <int NA, int NB>
+__global__ void __launch_bounds__(kBlk) k_contract(const ConMats m, int64_t total, int nb,
                                                   double* part) {
   typedef double D2 __attribute__((ext_vector_type(2)));
-  double v = 0.0;
+  double v[NA][NB];
+#pragma unroll
+  for (int i = 0; i < NA; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) v[i][j] = 0.0;
   const int64_t pairs = total / 2;
   for (int64_t q = (int64_t)blockIdx.x * kBlk + threadIdx.x; q < pairs;
        q += (int64_t)gridDim.x * kBlk) {
-    const D2 a = ((const D2*)A)[q], b = ((const D2*)B)[q];
-    v += a[0] * b[0] + a[1] * b[1];
+    D2 a[NA], b[NB];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) a[i] = ((const D2*)m.a[i])[q];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) b[j] = ((const D2*)m.b[j])[q];
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) v[i][j] += a[i][0] * b[j][0] + a[i][1] * b[j][1];
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0 && (total & 1)) v += A[total - 1] * B[total - 1];
-  v = block_sum(v);
-  if (threadIdx.x == 0) part[blockIdx.x] = v;
+#pragma unroll
+  for (int i = 0; i < NA; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      if (blockIdx.x == 0 && threadIdx.x == 0 && (total & 1))
+        v[i][j] += m.a[i][total - 1] * m.b[j][total - 1];
+      const double s = block_sum(v[i][j]);
+      if (threadIdx.x == 0) part[(size_t)(i * nb + j) * kRedBlocks + blockIdx.x] = s;
+    }
 }
 
-__global__ void k_contract_final(const double* part, int nb, double* out) {
-  if (threadIdx.x != 0) return;
+// out[p] = sum of part[p * kRedBlocks ..), p = blockIdx.x
+__global__ void __launch_bounds__(kBlk) k_contract_final(const double* part, double* out) {
+  part += (size_t)blockIdx.x * kRedBlocks;
   double v = 0.0;
-  for (int i = 0; i < nb; ++i) v += part[i];
-  *out = v;
+  for (int i = threadIdx.x; i < kRedBlocks; i += kBlk) v += part[i];
+  v = block_sum(v);
+  if (threadIdx.x == 0) out[blockIdx.x] = v;
 }
 
-hipError_t launch_contract(const double* A, const double* B, int64_t n, double* part, double* out,
-                           hipStream_t s) {
-  hipLaunchKernelGGL(k_contract, dim3(kRedBlocks), dim3(kBlk), 0, s, A, B, n * n, part);
-  hipLaunchKernelGGL(k_contract_final, dim3(1), dim3(kWave), 0, s, part, kRedBlocks, out);
+template <int NA>
+static void contract_tile(int nj, const ConMats& m, int64_t total, int nb, double* part,
+                          hipStream_t s) {
+  switch (nj) {
+    case 1:
+      hipLaunchKernelGGL((k_contract<NA, 1>), dim3(kRedBlocks), dim3(kBlk), 0, s, m, total, nb,
+                         part);
+      break;
+    case 2:
+      hipLaunchKernelGGL((k_contract<NA, 2>), dim3(kRedBlocks), dim3(kBlk), 0, s, m, total, nb,
+                         part);
+      break;
+    default:
+      hipLaunchKernelGGL((k_contract<NA, 3>), dim3(kRedBlocks), dim3(kBlk), 0, s, m, total, nb,
+                         part);
+  }
+}
+
+hipError_t launch_contract(const double* const* A, int na, const double* const* B, int nb,
+                           int64_t n, double* part, double* out, hipStream_t s) {
+  for (int a0 = 0; a0 < na; a0 += kConA)
+    for (int b0 = 0; b0 < nb; b0 += kConB) {
+      const int ni = na - a0 < kConA ? na - a0 : kConA, nj = nb - b0 < kConB ? nb - b0 : kConB;
+      ConMats m;
+      for (int i = 0; i < kConA; ++i) m.a[i] = i < ni ? A[a0 + i] : nullptr;
+      for (int j = 0; j < kConB; ++j) m.b[j] = j < nj ? B[b0 + j] : nullptr;
+      double* p = part + ((size_t)a0 * nb + b0) * kRedBlocks;
+      switch (ni) {
+        case 1: contract_tile<1>(nj, m, n * n, nb, p, s); break;
+        case 2: contract_tile<2>(nj, m, n * n, nb, p, s); break;
+        default: contract_tile<3>(nj, m, n * n, nb, p, s);
+      }
+    }
+  hipLaunchKernelGGL(k_contract_final, dim3(na * nb), dim3(kBlk), 0, s, part, out);
   return hipGetLastError();
 }
 
@@ -444,13 +512,11 @@ __global__ void __launch_bounds__(kBlk) k_diff_norms(const double* a, const doub
   }
 }
 
-__global__ void k_diff_norms_final(const double* part, int nb, double* out) {
+__global__ void __launch_bounds__(kBlk) k_diff_norms_final(const double* part, int nb,
+                                                          double* out) {
+  const double d2 = serial_sum(part, nb);
+  const double a2 = serial_sum(part + nb, nb);
   if (threadIdx.x != 0) return;
-  double d2 = 0.0, a2 = 0.0;
-  for (int i = 0; i < nb; ++i) {
-    d2 += part[i];
-    a2 += part[nb + i];
-  }
   out[0] = d2;
   out[1] = a2;
 }
@@ -458,7 +524,7 @@ __global__ void k_diff_norms_final(const double* part, int nb, double* out) {
 hipError_t launch_diff_norms(const double* a, const double* b, int64_t n, double* part,
                              double* out, hipStream_t s) {
   hipLaunchKernelGGL(k_diff_norms, dim3(kRedBlocks), dim3(kBlk), 0, s, a, b, n * n, part);
-  hipLaunchKernelGGL(k_diff_norms_final, dim3(1), dim3(kWave), 0, s, part, kRedBlocks, out);
+  hipLaunchKernelGGL(k_diff_norms_final, dim3(1), dim3(kBlk), 0, s, part, kRedBlocks, out);
   return hipGetLastError();
 }
 
@@ -487,16 +553,20 @@ hipError_t launch_postdecide(LayerState* st, const TileItem* items, int n_items,
 }
 
 // ------------------------------------------------------------------ outputs
-// P (FP64, N x N) <- src (layer precision, padded).  For a response the
-// source buffer follows the D1 layer: S1 of layer d1_layer - 1 sits in
-// buffer (d1_layer - 1) & 1; without convergence the last layer's buffer.
+// P (FP64, N x N) <- src (layer precision, padded), output first + blockIdx.y:
+// 0 is S, 1 + j response j, whose source buffer follows the D1 layer: S1 of
+// layer d1_layer - 1 sits in buffer (d1_layer - 1) & 1; without convergence the
+// last layer's buffer.
 template <typename M>
-__global__ void __launch_bounds__(kBlk) k_copy_out(const LayerState* st, int which, const M* b0,
-                                                  const M* b1, int64_t ld, double* dst, int64_t n) {
-  const M* src = b0;
+__global__ void __launch_bounds__(kBlk) k_copy_out(const LayerState* st, int first, const M* s0,
+                                                  const MatList b0, const MatList b1, int64_t ld,
+                                                  const MatList dsts, int64_t n) {
+  const int which = first + (int)blockIdx.y - 1;
+  double* dst = (double*)dsts.p[which + 1];
+  const M* src = s0;
   if (which >= 0) {
     const int L = st->d1[which] && st->d1_layer[which] > 0 ? st->d1_layer[which] - 1 : st->n;
-    src = (L & 1) ? b1 : b0;
+    src = (const M*)((L & 1) ? b1.p[which] : b0.p[which]);
   }
   const int64_t total = n * n;
   for (int64_t q = (int64_t)blockIdx.x * kBlk + threadIdx.x; q < total;
@@ -506,26 +576,30 @@ __global__ void __launch_bounds__(kBlk) k_copy_out(const LayerState* st, int whi
   }
 }
 
-hipError_t launch_copy_out(dmpt_precision prec, const LayerState* st, int which, const void* b0,
-                           const void* b1, int64_t ld, double* dst, int64_t n, hipStream_t s) {
+hipError_t launch_copy_out(dmpt_precision prec, const LayerState* st, int first, int count,
+                           const void* s0, const MatList& b0, const MatList& b1, int64_t ld,
+                           const MatList& dst, int64_t n, hipStream_t s) {
   if (prec == DMPT_FP64)
-    hipLaunchKernelGGL(k_copy_out<double>, dim3(4096), dim3(kBlk), 0, s, st, which,
-                       (const double*)b0, (const double*)b1, ld, dst, n);
+    hipLaunchKernelGGL(k_copy_out<double>, dim3(4096, count), dim3(kBlk), 0, s, st, first,
+                       (const double*)s0, b0, b1, ld, dst, n);
   else
-    hipLaunchKernelGGL(k_copy_out<float>, dim3(4096), dim3(kBlk), 0, s, st, which, (const float*)b0,
-                       (const float*)b1, ld, dst, n);
+    hipLaunchKernelGGL(k_copy_out<float>, dim3(4096, count), dim3(kBlk), 0, s, st, first,
+                       (const float*)s0, b0, b1, ld, dst, n);
   return hipGetLastError();
 }
 
-__global__ void __launch_bounds__(kBlk) k_trace(const double* P, int64_t n, double* out) {
+// Tr P of output blockIdx.x into the state (0: P0, 1 + j: P1_j; NULL: zero)
+__global__ void __launch_bounds__(kBlk) k_trace(const MatList P, int64_t n, LayerState* st) {
+  const double* p = (const double*)P.p[blockIdx.x];
   double v = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += kBlk) v += P[i * n + i];
+  if (p)
+    for (int64_t i = threadIdx.x; i < n; i += kBlk) v += p[i * n + i];
   v = block_sum(v);
-  if (threadIdx.x == 0) *out = v;
+  if (threadIdx.x == 0) st->traces[blockIdx.x] = v;
 }
 
-hipError_t launch_trace(const double* P, int64_t n, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_trace, dim3(1), dim3(kBlk), 0, s, P, n, out);
+hipError_t launch_traces(const MatList& P, int count, int64_t n, LayerState* st, hipStream_t s) {
+  hipLaunchKernelGGL(k_trace, dim3(count), dim3(kBlk), 0, s, P, n, st);
   return hipGetLastError();
 }
 
@@ -576,7 +650,9 @@ hipError_t launch_from_f64(dmpt_precision prec, const double* A, int64_t n, int6
 // Plain copy of a padded layer-precision matrix into FP64 N x N (products check).
 hipError_t launch_copy_plain(dmpt_precision prec, const void* src, int64_t ld, double* dst,
                              int64_t n, hipStream_t s) {
-  return launch_copy_out(prec, nullptr, -1, src, src, ld, dst, n, s);
+  MatList none, out;
+  out.p[0] = dst;
+  return launch_copy_out(prec, nullptr, 0, 1, src, none, none, ld, out, n, s);
 }
 
 }  // namespace dmpt

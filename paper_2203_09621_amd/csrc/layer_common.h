@@ -135,6 +135,25 @@ static __device__ double block_min(double v) {
   return r;
 }
 
+// sum of part[0..nb) in index order by thread 0, whose loads would otherwise
+// wait on each other: the block brings them into LDS first.  The result is
+// valid in thread 0.
+constexpr int kStage = 1024;
+static __device__ double serial_sum(const double* part, int nb) {
+  __shared__ double sh[kStage];
+  double v = 0.0;
+  for (int i0 = 0; i0 < nb; i0 += kStage) {
+    const int m = nb - i0 < kStage ? nb - i0 : kStage;
+    __syncthreads();
+    for (int i = threadIdx.x; i < m; i += kBlk) sh[i] = part[i0 + i];
+    __syncthreads();
+    if (threadIdx.x == 0)
+#pragma unroll 16
+      for (int i = 0; i < m; ++i) v += sh[i];
+  }
+  return v;
+}
+
 // Split scale: choose e with max|Y| 2^e in [1/16, 1/8), leaving room for the
 // growth of one layer before the next choice.
 static __device__ __forceinline__ int split_exponent(double m) {
