@@ -73,7 +73,7 @@ typedef struct {
   int32_t precision;       /* dmpt_precision; default DMPT_SPLIT_FP16 */
   int32_t max_layers;      /* default 100, at most DMPT_MAX_LAYERS */
   int32_t check_symmetry;  /* nonzero: dmpt_init / dmpt_response verify exact symmetry (EASYM) */
-  int32_t poll_every;      /* host checks the device stop flag every this many layers (0 = auto) */
+  int32_t poll_every;      /* layers the host enqueues ahead of the device's stop flag (0 = auto) */
   int32_t timing;          /* nonzero: time every layer-product launch with hipEvents on the
                               context's stream (dmpt_stats.product_ms / product_launches) */
   int32_t ckpt_every;      /* > 0: dmpt_response keeps (S, S1) every this many layers so that

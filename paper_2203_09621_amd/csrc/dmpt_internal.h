@@ -256,14 +256,22 @@ hipError_t launch_decide0(dmpt_precision prec, LayerState* st, const void* x, in
 hipError_t launch_update(dmpt_precision prec, const LayerState* st, int which, const void* x,
                          const void* s_old, void* dst, void* hi, void* lo, int64_t rows,
                          int64_t ld, int t, double* pfro, double* pmax, hipStream_t s);
+// Direct forms: the update of S and of responses 0 .. k-1 in one launch (x, s_old
+// and dst: entry 0 for S, 1 + j for response j), with update_blocks(rows * ld)
+// partials per matrix, and Algorithm 3 from them.
+int update_blocks(int64_t elems);
+hipError_t launch_update_all(dmpt_precision prec, const LayerState* st, int k, const MatList& x,
+                             const MatList& s_old, const MatList& dst, int64_t rows, int64_t ld,
+                             double* pfro0, double* pfro1, double* pmax1, hipStream_t s);
+// progress (pinned host memory): receives 2 n + done
 hipError_t launch_decide1(LayerState* st, const double* pfro0, const double* pfro1,
-                          const double* pmax1, int split, int lo_shift, hipStream_t s);
+                          const double* pmax1, int blocks, int32_t* progress, hipStream_t s);
 // Fused split layer: the decisions before the products (N_X from np trace
 // partials) and after them (item partials of `items`, slot = index).
 hipError_t launch_predecide(LayerState* st, const double* part, int np, hipStream_t s);
 hipError_t launch_postdecide(LayerState* st, const TileItem* items, int n_items,
                              const double* part_f, const double* part_m, int lo_shift,
-                             hipStream_t s);
+                             int32_t* progress, hipStream_t s);
 // Outputs first .. first + count - 1 (0: S from s0; 1 + j: response j from its
 // buffer b0.p[j] or b1.p[j]) into dst.p[output].
 hipError_t launch_copy_out(dmpt_precision prec, const LayerState* st, int first, int count,

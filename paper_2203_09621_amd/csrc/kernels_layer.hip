@@ -370,21 +370,61 @@ hipError_t launch_update(dmpt_precision prec, const LayerState* st, int which, c
 // the stop flag.
 __global__ void __launch_bounds__(kBlk) k_decide1(LayerState* st, const double* pfro0,
                                                  const double* pfro1, const double* pmax1,
-                                                 int split, int lo_shift) {
+                                                 int blocks, int32_t* progress) {
   Partials pr;
   pr.fro0 = pfro0;
-  pr.n0 = kRedBlocks;
+  pr.n0 = blocks;
   for (int j = 0; j < kMaxK; ++j) {
     pr.fro1[j] = pfro1 + (size_t)j * kRedBlocks;
     pr.max1[j] = pmax1 + (size_t)j * kRedBlocks;
-    pr.n1[j] = kRedBlocks;
+    pr.n1[j] = blocks;
   }
-  decide1_body(st, pr, split, lo_shift);
+  decide1_body(st, pr, 0, 0);
+  if (threadIdx.x == 0) report_progress(st, progress);
 }
 
 hipError_t launch_decide1(LayerState* st, const double* pfro0, const double* pfro1,
-                          const double* pmax1, int split, int lo_shift, hipStream_t s) {
-  hipLaunchKernelGGL(k_decide1, dim3(1), dim3(kBlk), 0, s, st, pfro0, pfro1, pmax1, split, lo_shift);
+                          const double* pmax1, int blocks, int32_t* progress, hipStream_t s) {
+  hipLaunchKernelGGL(k_decide1, dim3(1), dim3(kBlk), 0, s, st, pfro0, pfro1, pmax1, blocks,
+                     progress);
+  return hipGetLastError();
+}
+
+// The update of a layer of the direct forms: S (blockIdx.y = 0) and response
+// blockIdx.y - 1 in one launch.  A pass over memory: below N ~ 2000 the matrices
+// sit in the caches and the launch itself (5 us a matrix) is what it costs, so all
+// matrices share one.  Taking Algorithm 3 in the last workgroup to finish instead
+// of a launch of its own was slower: the tickets (device-wide atomics) of 3072
+// workgroups cost 88 us a layer, of 150 workgroups 10 us.
+template <typename M>
+__global__ void __launch_bounds__(kBlk) k_update_all(const LayerState* st, const MatList x,
+                                                    const MatList s_old, const MatList dst,
+                                                    int64_t vecs, double* pfro0, double* pfro1,
+                                                    double* pmax1) {
+  const int o = blockIdx.y;
+  double* pf = o == 0 ? pfro0 : pfro1 + (size_t)(o - 1) * kRedBlocks;
+  double* pm = o == 0 ? nullptr : pmax1 + (size_t)(o - 1) * kRedBlocks + blockIdx.x;
+  update_body<M, _Float16, false>(st, o - 1, (const M*)x.p[o], (const M*)s_old.p[o], (M*)dst.p[o],
+                                  nullptr, nullptr, (int64_t)blockIdx.x * kBlk + threadIdx.x,
+                                  vecs, (int64_t)gridDim.x * kBlk, 1, 0, 0, pf + blockIdx.x, pm);
+}
+
+int update_blocks(int64_t elems) {
+  // one vector of four per thread, up to kRedBlocks workgroups per matrix
+  const int64_t need = (elems / 4 + kBlk - 1) / kBlk;
+  return (int)(need < kRedBlocks ? need : kRedBlocks);
+}
+
+hipError_t launch_update_all(dmpt_precision prec, const LayerState* st, int k, const MatList& x,
+                             const MatList& s_old, const MatList& dst, int64_t rows, int64_t ld,
+                             double* pfro0, double* pfro1, double* pmax1, hipStream_t s) {
+  const dim3 grid(update_blocks(rows * ld), 1 + k);
+  if (prec == DMPT_FP64)
+    hipLaunchKernelGGL(k_update_all<double>, grid, dim3(kBlk), 0, s, st, x, s_old, dst,
+                       rows * ld / 4, pfro0, pfro1, pmax1);
+  else
+    hipLaunchKernelGGL(k_update_all<float>, grid, dim3(kBlk), 0, s, st, x, s_old, dst,
+                       rows * ld / 4, pfro0, pfro1, pmax1);
   return hipGetLastError();
 }
 
@@ -540,15 +580,17 @@ hipError_t launch_predecide(LayerState* st, const double* part, int np, hipStrea
 
 __global__ void __launch_bounds__(kBlk) k_postdecide(LayerState* st, const TileItem* items,
                                                     int n_items, const double* part_f,
-                                                    const double* part_m, int lo_shift) {
+                                                    const double* part_m, int lo_shift,
+                                                    int32_t* progress) {
   postdecide_body(st, items, n_items, part_f, part_m, lo_shift);
+  if (threadIdx.x == 0) report_progress(st, progress);
 }
 
 hipError_t launch_postdecide(LayerState* st, const TileItem* items, int n_items,
                              const double* part_f, const double* part_m, int lo_shift,
-                             hipStream_t s) {
+                             int32_t* progress, hipStream_t s) {
   hipLaunchKernelGGL(k_postdecide, dim3(1), dim3(kBlk), 0, s, st, items, n_items, part_f, part_m,
-                     lo_shift);
+                     lo_shift, progress);
   return hipGetLastError();
 }
 

@@ -154,6 +154,12 @@ static __device__ double serial_sum(const double* part, int nb) {
   return v;
 }
 
+// Layer and stop flag of a response for the host (pinned memory): 2 n + done.
+static __device__ __forceinline__ void report_progress(const LayerState* st, int32_t* host) {
+  __hip_atomic_store(host, 2 * st->n + (st->done ? 1 : 0), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Split scale: choose e with max|Y| 2^e in [1/16, 1/8), leaving room for the
 // growth of one layer before the next choice.
 static __device__ __forceinline__ int split_exponent(double m) {
