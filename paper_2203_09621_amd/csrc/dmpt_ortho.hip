@@ -32,17 +32,51 @@ __global__ void __launch_bounds__(kBlk) k_scaled_identity(M* z, double c, int64_
   }
 }
 
-// Q = a0 I + a1 X + a2 T on the N x N block (T = X^2), zero elsewhere.
+// The first iterate's products with Z_0 = c I: X = (c O) c on the N x N block, zero
+// elsewhere, the lower triangle of O standing for both.  One term of every dot
+// product is not zero, so this is what the product kernels give, bit for bit (adding
+// 0 makes a zero term's sign theirs), at the cost of a pass over memory: at N = 4096
+// in FP64 0.05 ms in place of 2.0 + 1.3 ms.  A workgroup reads a 32 x 32 tile of the
+// lower triangle by rows and writes it and, through the LDS, its mirror by rows.
+constexpr int kMirTile = 32;
 template <typename M>
+__global__ void __launch_bounds__(kBlk) k_first_x(const M* o, double c, M* x, int64_t n,
+                                                 int64_t ld) {
+  __shared__ M sh[kMirTile][kMirTile + 1];
+  const int ti = blockIdx.y, tj = blockIdx.x;
+  if (tj > ti) return;
+  const M cm = (M)c;
+  const int col = threadIdx.x % kMirTile, row0 = threadIdx.x / kMirTile;
+  const int64_t i0 = (int64_t)ti * kMirTile, j0 = (int64_t)tj * kMirTile;
+  for (int row = row0; row < kMirTile; row += kBlk / kMirTile) {
+    const int64_t i = i0 + row, j = j0 + col;
+    M v = (M)0;
+    if (i < n && j < n) {
+      const M y = cm * o[i * ld + j] + (M)0;
+      v = y * cm + (M)0;
+    }
+    sh[row][col] = v;
+    if (j <= i) x[i * ld + j] = v;
+  }
+  __syncthreads();
+  for (int row = row0; row < kMirTile; row += kBlk / kMirTile)
+    if (i0 + col > j0 + row) x[(j0 + row) * ld + i0 + col] = sh[col][row];
+}
+
+// Q = a0 I + a1 X + a2 T on the N x N block (T = X^2), zero elsewhere; q may be t.
+// FIRST: c Q, the update Z_0 Q of the first iterate.
+template <typename M, bool FIRST>
 __global__ void __launch_bounds__(kBlk) k_poly2(const M* x, const M* t, M* q, int64_t n,
-                                               int64_t total, int64_t ld) {
+                                               int64_t total, int64_t ld, double c) {
   const double a0 = 1.875, a1 = -1.25, a2 = 0.375;
   for (int64_t p = (int64_t)blockIdx.x * kBlk + threadIdx.x; p < total;
        p += (int64_t)gridDim.x * kBlk) {
     const int64_t i = p / ld, j = p - i * ld;
     double v = 0.0;
     if (i < n && j < n) v = (i == j ? a0 : 0.0) + a1 * (double)x[p] + a2 * (double)t[p];
-    q[p] = (M)v;
+    M w = (M)v;
+    if constexpr (FIRST) w = (M)c * w + (M)0;
+    q[p] = w;
   }
 }
 
@@ -72,12 +106,14 @@ dmpt_status ofail(dmpt_status s, const std::string& m) {
   return s;
 }
 
-// Workspace of the single products: padded matrices and the two item lists.
+// Workspace of the single products: padded matrices and the two item lists, in one
+// allocation (mapping and unmapping device memory costs about 0.1 ms per call and
+// 1 ms per GB).
 struct ProductWork {
   dmpt_precision prec;
   int64_t n = 0, np = 0, ld = 0;
   size_t eb = 0;
-  std::vector<void*> allocs;
+  char* base = nullptr;
   TileItem* items_sym = nullptr;
   TileItem* items_all = nullptr;
   int n_sym = 0, n_all = 0;
@@ -85,18 +121,13 @@ struct ProductWork {
   double* part = nullptr;
   double* dscal = nullptr;
 
-  hipError_t get(void** p, size_t bytes) {
-    *p = nullptr;
-    hipError_t e = hipMalloc(p, bytes);
-    if (e == hipSuccess) allocs.push_back(*p);
-    return e;
+  // An FP64 matrix that the product kernels can read where it lies: no padding to
+  // add, rows on their 16-byte loads.
+  bool in_place(const double* m) const {
+    return prec == DMPT_FP64 && np == n && ((uintptr_t)m & 15) == 0;
   }
-  hipError_t matrix(void** p) {
-    hipError_t e = get(p, (size_t)np * ld * eb);
-    if (e == hipSuccess) e = hipMemset(*p, 0, (size_t)np * ld * eb);
-    return e;
-  }
-  hipError_t init(dmpt_precision pr, int64_t nn) {
+  // the lists, scalars and `mats` matrices (mat[0 .. mats))
+  hipError_t init(dmpt_precision pr, int64_t nn, int mats, void** mat, hipStream_t s) {
     prec = pr;
     n = nn;
     const int tile = product_tile(prec);
@@ -109,17 +140,26 @@ struct ProductWork {
     const int Ta = (int)((n + tile_all.edge - 1) / tile_all.edge);
     n_sym = Ts * (Ts + 1) / 2;
     n_all = Ta * Ta;
-    std::vector<TileItem> sym(n_sym), all(n_all);
-    product_items(Ts, 1, sym.data());
-    product_items(Ta, 2, all.data());
-    hipError_t e = get((void**)&items_sym, sym.size() * sizeof(TileItem));
-    if (e == hipSuccess) e = get((void**)&items_all, all.size() * sizeof(TileItem));
-    if (e == hipSuccess)
-      e = hipMemcpy(items_sym, sym.data(), sym.size() * sizeof(TileItem), hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-      e = hipMemcpy(items_all, all.data(), all.size() * sizeof(TileItem), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = get((void**)&part, 3 * 512 * sizeof(double));
-    if (e == hipSuccess) e = get((void**)&dscal, 16 * sizeof(double));
+    std::vector<TileItem> items(n_sym + n_all);
+    product_items(Ts, 1, items.data());
+    product_items(Ta, 2, items.data() + n_sym);
+    const size_t item_bytes = items.size() * sizeof(TileItem);
+    const size_t mbytes = (size_t)np * ld * eb;             // a multiple of 64 KB
+    const size_t small = (3 * 512 + 16) * sizeof(double);
+    hipError_t e = hipMalloc((void**)&base, mats * mbytes + small + item_bytes);
+    if (e != hipSuccess) {
+      base = nullptr;
+      return e;
+    }
+    for (int i = 0; i < mats; ++i) mat[i] = base + i * mbytes;
+    part = (double*)(base + mats * mbytes);
+    dscal = part + 3 * 512;
+    items_sym = (TileItem*)(dscal + 16);
+    items_all = items_sym + n_sym;
+    e = hipMemcpy(items_sym, items.data(), item_bytes, hipMemcpyHostToDevice);
+    // padding that a product reads but none writes; without padding every element
+    // is written before it is read
+    if (e == hipSuccess && np != n) e = hipMemsetAsync(base, 0, mats * mbytes, s);
     return e;
   }
   // C = A B (A, B symmetric); symmetric C on mirrored upper tiles, else every tile
@@ -139,7 +179,7 @@ struct ProductWork {
     return launch_products(prec, a, s);
   }
   ~ProductWork() {
-    for (void* p : allocs) (void)hipFree(p);
+    if (base) (void)hipFree(base);
   }
 };
 
@@ -163,12 +203,12 @@ dmpt_status dmpt_inverse_factor(int32_t precision, const double* O, int64_t N, d
   hipStream_t s = (hipStream_t)stream;
   const dmpt_precision prec = (dmpt_precision)precision;
   ProductWork w;
-  void *om = nullptr, *z = nullptr, *y = nullptr, *x = nullptr, *t = nullptr, *q = nullptr;
-  hipError_t e = w.init(prec, N);
-  for (void** p : {&om, &z, &y, &x, &t, &q})
-    if (e == hipSuccess) e = w.matrix(p);
+  void* m[5] = {};
+  hipError_t e = w.init(prec, N, 5, m, s);
   if (e != hipSuccess)
     return ofail(e == hipErrorOutOfMemory ? DMPT_ENOMEM : DMPT_EHIP, "workspace allocation failed");
+  void *z = m[0], *y = m[1], *x = m[2], *t = m[3], *q = t;
+  const void* om = m[4];
   const int64_t total = w.np * w.ld;
   double eps[2] = {0.0, 0.0};
   e = launch_gershgorin(O, N, w.part, nullptr, w.dscal, s);
@@ -177,21 +217,31 @@ dmpt_status dmpt_inverse_factor(int32_t precision, const double* O, int64_t N, d
   if (e != hipSuccess) return ofail(DMPT_EHIP, hipGetErrorString(e));
   if (!(eps[1] > 0.0) || !isfinite(eps[1]))
     return ofail(DMPT_ENONFINITE, "overlap matrix without a positive spectral bound");
-  e = launch_from_f64(prec, O, N, w.np, w.ld, 0, 0, om, nullptr, nullptr, s);
+  if (w.in_place(O))
+    om = O;
+  else
+    e = launch_from_f64(prec, O, N, w.np, w.ld, 0, 0, m[4], nullptr, nullptr, s);
   if (e != hipSuccess) return ofail(DMPT_EHIP, hipGetErrorString(e));
   const double c = 1.0 / sqrt(eps[1]);
-  if (prec == DMPT_FP64)
-    hipLaunchKernelGGL(k_scaled_identity<double>, dim3(2048), dim3(kBlk), 0, s, (double*)z, c, N,
-                       total, w.ld);
-  else
-    hipLaunchKernelGGL(k_scaled_identity<float>, dim3(2048), dim3(kBlk), 0, s, (float*)z, c, N,
-                       total, w.ld);
   int it = 0;
   double r = INFINITY;
   for (;; ++it) {
-    // X = Z O Z (Y = Z O, general; X = Y Z, symmetric)
-    e = w.product(z, om, y, false, s);
-    if (e == hipSuccess) e = w.product(y, z, x, true, s);
+    // X = Z O Z (Y = Z O, general; X = Y Z, symmetric).  Y is formed in full although
+    // Z and O commute: with its lower half mirrored the recursion loses the
+    // stability that its rounding errors need (on a matrix of condition 100 the
+    // residual grew sevenfold with every step past convergence).
+    if (it == 0) {
+      const dim3 grid((unsigned)(w.np / kMirTile), (unsigned)(w.np / kMirTile));
+      if (prec == DMPT_FP64)
+        hipLaunchKernelGGL(k_first_x<double>, grid, dim3(kBlk), 0, s, (const double*)om, c,
+                           (double*)x, N, w.ld);
+      else
+        hipLaunchKernelGGL(k_first_x<float>, grid, dim3(kBlk), 0, s, (const float*)om, c,
+                           (float*)x, N, w.ld);
+    } else {
+      e = w.product(z, om, y, false, s);
+      if (e == hipSuccess) e = w.product(y, z, x, true, s);
+    }
     if (e != hipSuccess) break;
     if (prec == DMPT_FP64)
       hipLaunchKernelGGL(k_dev_identity<double>, dim3(512), dim3(kBlk), 0, s, (const double*)x, N,
@@ -213,17 +263,34 @@ dmpt_status dmpt_inverse_factor(int32_t precision, const double* O, int64_t N, d
     // Z <- Z (a0 I + a1 X + a2 X^2)
     e = w.product(x, x, t, true, s);
     if (e != hipSuccess) break;
+    if (it == 0) {
+      if (prec == DMPT_FP64)
+        hipLaunchKernelGGL((k_poly2<double, true>), dim3(2048), dim3(kBlk), 0, s, (const double*)x,
+                           (const double*)t, (double*)z, N, total, w.ld, c);
+      else
+        hipLaunchKernelGGL((k_poly2<float, true>), dim3(2048), dim3(kBlk), 0, s, (const float*)x,
+                           (const float*)t, (float*)z, N, total, w.ld, c);
+      continue;
+    }
     if (prec == DMPT_FP64)
-      hipLaunchKernelGGL(k_poly2<double>, dim3(2048), dim3(kBlk), 0, s, (const double*)x,
-                         (const double*)t, (double*)q, N, total, w.ld);
+      hipLaunchKernelGGL((k_poly2<double, false>), dim3(2048), dim3(kBlk), 0, s, (const double*)x,
+                         (const double*)t, (double*)q, N, total, w.ld, c);
     else
-      hipLaunchKernelGGL(k_poly2<float>, dim3(2048), dim3(kBlk), 0, s, (const float*)x,
-                         (const float*)t, (float*)q, N, total, w.ld);
+      hipLaunchKernelGGL((k_poly2<float, false>), dim3(2048), dim3(kBlk), 0, s, (const float*)x,
+                         (const float*)t, (float*)q, N, total, w.ld, c);
     e = w.product(z, q, y, true, s);
     if (e != hipSuccess) break;
     std::swap(z, y);
   }
   if (e != hipSuccess) return ofail(DMPT_EHIP, hipGetErrorString(e));
+  if (it == 0) {                               // Z_0 = c I
+    if (prec == DMPT_FP64)
+      hipLaunchKernelGGL(k_scaled_identity<double>, dim3(2048), dim3(kBlk), 0, s, (double*)z, c, N,
+                         total, w.ld);
+    else
+      hipLaunchKernelGGL(k_scaled_identity<float>, dim3(2048), dim3(kBlk), 0, s, (float*)z, c, N,
+                         total, w.ld);
+  }
   e = launch_copy_plain(prec, z, w.ld, Z, N, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return ofail(DMPT_EHIP, hipGetErrorString(e));
@@ -242,17 +309,28 @@ dmpt_status dmpt_congruence(int32_t precision, int64_t N, const double* Z, const
   hipStream_t s = (hipStream_t)stream;
   const dmpt_precision prec = (dmpt_precision)precision;
   ProductWork w;
-  void *zm = nullptr, *am = nullptr, *y = nullptr, *r = nullptr;
-  hipError_t e = w.init(prec, N);
-  for (void** p : {&zm, &am, &y, &r})
-    if (e == hipSuccess) e = w.matrix(p);
+  void* m[3] = {};
+  // Y and, where the operands cannot be read or the result not be written in place
+  // (Y Z is written while Z is read), copies of Z and of A, which the result replaces
+  w.prec = prec;
+  w.n = N;
+  w.np = (N + product_tile(prec) - 1) / product_tile(prec) * product_tile(prec);
+  const double* end = Z + (size_t)N * N;
+  const bool direct = w.in_place(Z) && w.in_place(A) &&
+                      (out + (size_t)N * N <= Z || out >= end);
+  hipError_t e = w.init(prec, N, direct ? 1 : 3, m, s);
   if (e != hipSuccess)
     return ofail(e == hipErrorOutOfMemory ? DMPT_ENOMEM : DMPT_EHIP, "workspace allocation failed");
-  e = launch_from_f64(prec, Z, N, w.np, w.ld, 0, 0, zm, nullptr, nullptr, s);
-  if (e == hipSuccess) e = launch_from_f64(prec, A, N, w.np, w.ld, 0, 0, am, nullptr, nullptr, s);
-  if (e == hipSuccess) e = w.product(zm, am, y, false, s);    // Y = Z A
-  if (e == hipSuccess) e = w.product(y, zm, r, true, s);      // Z A Z
-  if (e == hipSuccess) e = launch_copy_plain(prec, r, w.ld, out, N, s);
+  if (direct) {
+    e = w.product(Z, A, m[0], false, s);                           // Y = Z A
+    if (e == hipSuccess) e = w.product(m[0], Z, out, true, s);     // Z A Z
+  } else {
+    e = launch_from_f64(prec, Z, N, w.np, w.ld, 0, 0, m[1], nullptr, nullptr, s);
+    if (e == hipSuccess) e = launch_from_f64(prec, A, N, w.np, w.ld, 0, 0, m[2], nullptr, nullptr, s);
+    if (e == hipSuccess) e = w.product(m[1], m[2], m[0], false, s);
+    if (e == hipSuccess) e = w.product(m[0], m[1], m[2], true, s);
+    if (e == hipSuccess) e = launch_copy_plain(prec, m[2], w.ld, out, N, s);
+  }
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   return e == hipSuccess ? DMPT_OK : ofail(DMPT_EHIP, hipGetErrorString(e));
 }
