@@ -689,6 +689,16 @@ dmpt_status run_response(dmpt_ctx* c, const double* const* H1, int k1, bool orde
   auto save_ckpt = [&](int layer) -> hipError_t {
     const int slot = layer / c->ckpt;
     if (slot >= c->nslots) return hipSuccess;
+    if (split) {
+      MatList src, dst;
+      src.p[0] = c->s_master;
+      dst.p[0] = c->ck_s[slot];
+      for (int j = 0; j < k; ++j) {
+        src.p[1 + j] = c->s1buf[j][layer & 1];
+        dst.p[1 + j] = c->ck_s1[(size_t)slot * c->k_max + j];
+      }
+      return launch_copy_masters(src, dst, 1 + k, np, ld, s);
+    }
     hipError_t e2 = hipMemcpyAsync(c->ck_s[slot], c->s_master, mbytes, hipMemcpyDeviceToDevice, s);
     for (int j = 0; j < k && e2 == hipSuccess; ++j)
       e2 = hipMemcpyAsync(c->ck_s1[(size_t)slot * c->k_max + j], c->s1buf[j][layer & 1], mbytes,

@@ -222,12 +222,11 @@ __global__ void __launch_bounds__(kBlk) k_b_postdecide(const BatchProblem* P, co
 }
 
 // ------------------------------------------------------------------ outputs
-// The pair launch keeps only the upper triangle of the FP32 masters current
-// (its mirror pass writes the 16-bit splits alone; the recursion reads the
+// The product launches keep only the upper triangle of the FP32 masters current
+// (their mirror pass writes the 16-bit splits alone; the recursion reads the
 // masters only on upper tiles), so output block (bi, bj) is read from the
 // upper block (min, max) in coalesced rows and written through LDS,
-// transposed below the diagonal.  The 256-row launch's full masters are
-// symmetric, so the same read serves them.
+// transposed below the diagonal.
 __global__ void __launch_bounds__(kBlk) k_b_out(const BatchProblem* P, const OutBlock* B,
                                                double* const* p0tab, double* const* p1tab) {
   __shared__ float tile[kOutB][kOutB + 1];

@@ -274,6 +274,8 @@ hipError_t launch_postdecide(LayerState* st, const TileItem* items, int n_items,
                              int32_t* progress, hipStream_t s);
 // Outputs first .. first + count - 1 (0: S from s0; 1 + j: response j from its
 // buffer b0.p[j] or b1.p[j]) into dst.p[output].
+hipError_t launch_copy_masters(const MatList& src, const MatList& dst, int count, int64_t rows,
+                               int64_t ld, hipStream_t s);
 hipError_t launch_copy_out(dmpt_precision prec, const LayerState* st, int first, int count,
                            const void* s0, const MatList& b0, const MatList& b1, int64_t ld,
                            const MatList& dst, int64_t n, hipStream_t s);

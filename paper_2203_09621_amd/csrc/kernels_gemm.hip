@@ -49,6 +49,333 @@ __device__ __forceinline__ int64_t uni(int64_t x) {
 template <typename T>
 __device__ __forceinline__ T* uni(T* p) { return (T*)uni((int64_t)p); }
 
+// Memory that no kernel writes while the product launch runs (the items, the
+// problem descriptors, the layer states, which the decision kernels write
+// between launches), read through the constant address space: workgroup-
+// uniform reads then become scalar loads, which do not queue behind the
+// vector loads in flight and are not counted with them, and what is derived
+// from them stays in scalar registers (in vector registers the branches on them
+// are divergent to the compiler, which then keeps them, and spills them, per lane).
+template <typename T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T* cst(const T* p) {
+  return (const __attribute__((address_space(4))) T*)p;
+}
+
+// An item as its five words (out | prob << 16, ti, tj, ti2, tj2).
+__device__ __forceinline__ TileItem item_at(const TileItem* items, int id) {
+  const auto* w = cst((const uint32_t*)(items + id));
+  const uint32_t w0 = w[0];
+  TileItem it;
+  it.out = (int16_t)(w0 & 0xffffu);
+  it.prob = (int16_t)(w0 >> 16);
+  it.ti = (int32_t)w[1];
+  it.tj = (int32_t)w[2];
+  it.ti2 = (int32_t)w[3];
+  it.tj2 = (int32_t)w[4];
+  return it;
+}
+
+// ------------------------------------------------------------------ fused epilogue
+// The layer update of a product tile (k_products_split in fused launches, and
+// k_products_pair).  The accumulators go through the LDS in rounds of SR rows: the
+// waves park one 32-row fragment strip each, then every thread takes groups of four
+// columns of a row (direct pass: update, norms, splits, coalesced stores) and leaves
+// the splits in place of X, packed hi << 16 | lo, and last the columns are read back
+// as rows of the mirror tile (mirror pass: 16-bit splits alone, since the next
+// products read whole row panels).  The FP32 masters are current on and above the
+// diagonal only; what reads them reads the upper triangle.
+// Element (lr, lc) of the upper triangle stands for itself and its mirror, so the
+// norms weigh it 2 (off the diagonal) or 1 (on it).
+// What bounds it: instructions and waits.  A workgroup has one or two waves per SIMD,
+// which issue one instruction every four cycles and have nothing to hide a wait
+// behind.  Per condition of the general case (diagonal tiles, tiles past the edge)
+// and element, with a 64-bit address per access, four columns took about 250
+// instructions in each pass; generic pointers made every wait for the LDS a wait for
+// the stores too, and the old values were waited for batch by batch behind the
+// stores of the batch before.  Whole tiles off the diagonal now have a path of their
+// own (42 and 14 instructions), addresses advance by uniform steps, the accesses are
+// global ones and the old values are loaded ahead.  Per response tile: 256 x 256 at
+// N = 4096 104 -> 35 us (main loop 616 -> 560 us with scalar operand addresses),
+// at N = 16384 91 -> 30 us; 128 x 128 at N = 1001 15.5 -> 7.4 us.  All tiles of a
+// round end together, and what they write then (768 KB each) bounds the rest.
+// Float (row tr, column c) of the staged strip lies at slot c / 4 ^ f(tr / 4) of its
+// row: park (32 columns of rows 4 apart), direct pass (a row) and mirror pass (four
+// columns of 16 row groups) all touch every bank.
+__device__ __forceinline__ int park_swz(int quad) { return (quad >> 1) | ((quad & 1) << 3); }
+
+template <typename T16, int NT, int SR, int BN, int WTM, int TILE>
+struct Epilogue {
+  static constexpr int RS = 4 * NT / BN;       // staged rows of one round of groups
+  static constexpr int ITER = SR / RS;         // groups of four per thread, direct pass
+  static constexpr int LS = NT / (SR / 4);     // mirror rows of one round
+  static constexpr int MITER = BN / LS;
+  static constexpr int H = BN / TILE;          // tiles side by side (2: pair)
+  static constexpr int G = 4;                  // groups of one batch of loads and stores
+  static constexpr int NG = ITER / G, MG = MITER / G;
+  static_assert(SR == 64 && RS * ITER == SR && LS * MITER == BN, "geometry");
+  static_assert((RS == 4 || RS == 8) && 32 % (RS * G) == 0, "a batch lies in one strip of 32 rows");
+  static_assert(TILE % (LS * G) == 0, "a mirror batch lies in one tile");
+  typedef uint16_t U4 __attribute__((ext_vector_type(4)));
+  typedef uint32_t P4 __attribute__((ext_vector_type(4)));
+
+  // pointers that come from memory are generic to the compiler, and a flat access
+  // counts as an LDS access too: every wait for the LDS would wait for the stores
+  template <typename P> using Glob = __attribute__((address_space(1))) P*;
+
+  // uniform
+  int64_t ld;
+  int sig, esplit;
+  bool upd, diff, need_old, fast;
+
+  // the state's flags (it.out == 0: X and S, else response j and S1_j), in scalars
+  template <typename St>                       // pointer to the LayerState
+  __device__ __forceinline__ void flags(St st, int out, int64_t stride) {
+    ld = uni(stride);
+    sig = uni((int)st->sigma_cur);
+    upd = uni(out == 0 ? (int)st->upd_s0 : 1) != 0;
+    // ||S - X||_F^2 at the D0 layer, ||S1_j - X1_j||_F^2 once D0 converged
+    diff = out == 0 ? !upd : uni((int)st->d0) != 0;
+    need_old = diff || sig < 0;
+    esplit = out == 0 ? 0 : uni((int)st->s1_exp_next[out - 1]);
+  }
+  // of this thread
+  int tid, tr0, c4, lcl;                       // direct: staged row, column / 4, tile column
+  bool on, diag;                               // direct: its tile exists, is diagonal
+  int rows_ok;                                 // direct: rows of the tile that exist
+  Glob<const float> mr;                        // old values, (tile row tr0, its columns)
+  Glob<float> mw;
+  Glob<uint16_t> hd, lo_d;                        // direct splits
+  Glob<uint16_t> hm[H], lm[H];                 // mirror splits of tile h, row tid / 16
+  int mq, mlr;                                 // mirror: quad of rows, first tile row
+  bool mon[H], mdiag[H];
+  int mrows_ok[H], mcols_ok[H];
+
+  // tile h at (r0, c0); kd: rows and columns that exist
+  __device__ __forceinline__ void init(int thread, const int64_t* r0, const int64_t* c0, int64_t kd,
+                                       int64_t pdim, int tiles, const float* Mr, float* Mw,
+                                       uint16_t* Hw, uint16_t* Lw) {
+    tid = thread;
+    tr0 = tid / (BN / 4);
+    c4 = tid % (BN / 4);
+    const int h = H == 1 ? 0 : c4 / (TILE / 4);
+    lcl = c4 * 4 - h * TILE;
+    const int64_t rh = H == 1 ? r0[0] : (h ? r0[H - 1] : r0[0]);
+    const int64_t ch = H == 1 ? c0[0] : (h ? c0[H - 1] : c0[0]);
+    on = h < tiles && ch + lcl < kd;           // four columns from a multiple of 4
+    diag = rh == ch;
+    rows_ok = (int)(kd - rh < TILE ? kd - rh : TILE);
+    mr = (Glob<const float>)Mr + (rh + tr0) * ld + ch + lcl;
+    mw = (Glob<float>)Mw + (rh + tr0) * ld + ch + lcl;
+    const int64_t pi = panel_index(rh + tr0, ch + lcl, pdim);
+    hd = (Glob<uint16_t>)Hw + pi;
+    lo_d = (Glob<uint16_t>)Lw + pi;
+    mq = tid % (SR / 4);
+    mlr = (mq / 8) * WTM + (mq % 8) * 4;
+    bool whole = tiles == H;
+#pragma unroll
+    for (int t = 0; t < H; ++t) {
+      mon[t] = t < tiles;
+      mdiag[t] = r0[t] == c0[t];
+      mrows_ok[t] = (int)(kd - c0[t] < TILE ? kd - c0[t] : TILE);
+      mcols_ok[t] = (int)(kd - r0[t] < TILE ? kd - r0[t] : TILE);
+      if (mdiag[t] || mrows_ok[t] < TILE || mcols_ok[t] < TILE) whole = false;
+      const int64_t mi = panel_index(c0[t] + tid / (SR / 4), r0[t] + mlr, pdim);
+      hm[t] = (Glob<uint16_t>)Hw + mi;
+      lm[t] = (Glob<uint16_t>)Lw + mi;
+    }
+    fast = uni((int)whole) != 0;
+  }
+
+  // tile row of the first group of batch g of round m, less tr0
+  static __device__ __forceinline__ int row(int m, int g) {
+    const int r = g * G * RS;
+    return (r / 32) * WTM + m * 32 + r % 32;
+  }
+
+  // old values of a batch (of the elements that exist), of LB batches
+  __device__ __forceinline__ void load(int m, int g, f32x4* so) const {
+    if (!need_old) return;
+    const int r = row(m, g);
+    Glob<const float> p = mr + r * ld;
+#pragma unroll
+    for (int i = 0; i < G; ++i)
+      if (on && r + i * RS + tr0 < rows_ok) so[i] = *(Glob<const f32x4>)(p + i * RS * ld);
+  }
+  template <int LB>
+  __device__ __forceinline__ void load_step(int m, int g0, f32x4* so) const {
+    if (!need_old) return;
+#pragma unroll
+    for (int g = 0; g < LB; ++g) {
+      Glob<const float> p = mr + row(m, g0 + g) * ld;
+#pragma unroll
+      for (int i = 0; i < G; ++i, p += RS * ld) so[g * G + i] = *(Glob<const f32x4>)p;
+    }
+  }
+
+  template <bool FAST>
+  __device__ __forceinline__ void direct(int m, int g, const f32x4* so, float* T, double& pf,
+                                         float& pm) const {
+    const int r = row(m, g);
+    Glob<float> mp = mw + r * ld;
+    Glob<uint16_t> hp = hd + r * kPanelK, lp = lo_d + r * kPanelK;
+    float* tb = T + (tr0 + g * G * RS) * BN;
+    float* tp[G];
+    f32x4 sn[G];
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+      const int quad = RS == 4 ? g * G + i : 2 * (g * G + i) + (tr0 >> 2);
+      tp[i] = tb + i * RS * BN + 4 * (c4 ^ park_swz(quad));
+      sn[i] = *(const f32x4*)tp[i];            // X
+    }
+    if (diff) {
+#pragma unroll
+      for (int i = 0; i < G; ++i) {
+        const int lr = r + i * RS + tr0;
+        if (!FAST && !(on && lr < rows_ok)) continue;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const double w = !FAST && diag ? (lr < lcl + q ? 2.0 : (lr == lcl + q ? 1.0 : 0.0)) : 2.0;
+          const double d = (double)so[i][q] - (double)sn[i][q];
+          pf += w * d * d;
+        }
+      }
+    }
+    if (sig < 0) {
+#pragma unroll
+      for (int i = 0; i < G; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sn[i][q] = 2.0f * so[i][q] - sn[i][q];
+    }
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+      const int lr = r + i * RS + tr0;
+      const bool ok = FAST || (on && lr < rows_ok);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float v = fabsf(sn[i][q]);
+        pm = fmaxf(pm, FAST || (ok && (!diag || lr <= lcl + q)) ? v : 0.0f);
+      }
+    }
+    if (!upd) return;
+#pragma unroll
+    for (int i = 0; i < G; ++i, mp += RS * ld) {
+      const int lr = r + i * RS + tr0;
+      if (!FAST && !(on && lr < rows_ok)) continue;
+      uint16_t h[4], l[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        split_one<T16>(sn[i][q], esplit, Split16<T16>::kShift, h + q, l + q);
+      *(P4*)tp[i] = P4{((uint32_t)h[0] << 16) | l[0], ((uint32_t)h[1] << 16) | l[1],
+                       ((uint32_t)h[2] << 16) | l[2], ((uint32_t)h[3] << 16) | l[3]};
+      if (FAST || !diag || lr <= lcl) {
+        *(Glob<f32x4>)mp = sn[i];
+        *(Glob<U4>)(hp + i * RS * kPanelK) = U4{h[0], h[1], h[2], h[3]};
+        *(Glob<U4>)(lp + i * RS * kPanelK) = U4{l[0], l[1], l[2], l[3]};
+      } else if (lr <= lcl + 3) {
+#pragma unroll
+        for (int q = 1; q < 4; ++q)
+          if (lr <= lcl + q) {
+            mp[q] = sn[i][q];
+            hp[i * RS * kPanelK + q] = h[q];
+            lp[i * RS * kPanelK + q] = l[q];
+          }
+      }
+    }
+  }
+
+  // rows tid / 16 + i LS of the mirror get the staged rows 4 mq .. 4 mq + 3 of
+  // that column
+  template <bool FAST>
+  __device__ __forceinline__ void mirror(int m, int g, const float* T) const {
+    const int f = park_swz(mq);
+    const int lr = mlr + m * 32;
+    const int t = g * G * LS / TILE;
+    const int row0 = g * G * LS - t * TILE;    // less tid / 16
+    const int64_t ofs = (int64_t)m * (kPanelRows * kPanelK) + row0 * kPanelK;
+    Glob<uint16_t> hp = (t ? hm[H - 1] : hm[0]) + ofs;
+    Glob<uint16_t> lp = (t ? lm[H - 1] : lm[0]) + ofs;
+    const bool dg = t ? mdiag[H - 1] : mdiag[0];
+    const int rows = t ? mrows_ok[H - 1] : mrows_ok[0], cols = t ? mcols_ok[H - 1] : mcols_ok[0];
+    if (!FAST && !(t ? mon[H - 1] : mon[0])) return;
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+      const int c = tid / (SR / 4) + row0 + i * LS;
+      if (!FAST && (c >= rows || lr >= cols || (dg && lr >= c))) continue;
+      const int lc = c + t * TILE;
+      const float* tp = T + 4 * mq * BN + 4 * ((lc >> 2) ^ f) + (lc & 3);
+      uint32_t u[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) u[q] = __builtin_bit_cast(uint32_t, tp[q * BN]);
+      const U4 h = U4{(uint16_t)(u[0] >> 16), (uint16_t)(u[1] >> 16), (uint16_t)(u[2] >> 16),
+                      (uint16_t)(u[3] >> 16)};
+      const U4 l = U4{(uint16_t)u[0], (uint16_t)u[1], (uint16_t)u[2], (uint16_t)u[3]};
+      if (FAST || !dg || lr + 3 < c) {
+        *(Glob<U4>)(hp + i * LS * kPanelK) = h;
+        *(Glob<U4>)(lp + i * LS * kPanelK) = l;
+      } else {
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+          if (lr + q < c) {
+            hp[i * LS * kPanelK + q] = h[q];
+            lp[i * LS * kPanelK + q] = l[q];
+          }
+      }
+    }
+  }
+
+  // All rounds; park(m) writes the fragments of round m to T.  The old values of a
+  // round are loaded ahead of the stores of the round before it: loads and stores
+  // count down in order, and with the loads of each batch between the stores of the
+  // batches every batch waited for the one before it to reach memory (3.5 us a
+  // batch of the 256-row tile; 13 of the 17 us of a round).
+  template <int ROUNDS, typename Park>
+  __device__ __forceinline__ void run(float* T, double& pf, float& pm, Park park) const {
+    constexpr int LB = NG > 2 ? 1 : 2;         // batches loaded together
+    constexpr int NS = NG / LB;                // such steps per round
+    constexpr int UM = NS % 2 ? 2 : 1;         // rounds after which the sets are in place again
+    static_assert(NG % LB == 0 && ROUNDS % UM == 0, "old values alternate between two sets");
+    const bool quick = fast && upd;
+    f32x4 so[2][LB * G] = {};
+    if (quick) load_step<LB>(0, 0, so[0]);
+#pragma unroll
+    for (int m2 = 0; m2 < ROUNDS; m2 += UM) {
+#pragma unroll
+      for (int p = 0; p < UM; ++p) {
+        const int m = m2 + p;
+        park(m);
+        lds_barrier();
+        if (quick) {
+#pragma unroll
+          for (int q = 0; q < NS; ++q) {
+            const int cur = (p * NS + q) & 1;
+            const bool last = q + 1 == NS;
+            load_step<LB>(last && m + 1 < ROUNDS ? m + 1 : m, last ? 0 : (q + 1) * LB, so[cur ^ 1]);
+#pragma unroll
+            for (int g = 0; g < LB; ++g) direct<true>(m, q * LB + g, so[cur] + g * G, T, pf, pm);
+          }
+          lds_barrier();
+#pragma unroll
+          for (int g = 0; g < MG; ++g) mirror<true>(m, g, T);
+          lds_barrier();
+        } else {
+#pragma unroll 1
+          for (int g = 0; g < NG; ++g) {
+            f32x4 old[G] = {};
+            load(m, g, old);
+            direct<false>(m, g, old, T, pf, pm);
+          }
+          lds_barrier();
+          if (upd) {
+#pragma unroll 1
+            for (int g = 0; g < MG; ++g) mirror<false>(m, g, T);
+            lds_barrier();
+          }
+        }
+      }
+    }
+  }
+};
+
 // ------------------------------------------------------------------ split form
 // Resolve the skip flags and the operand scale of one tile item.
 // Returns false when the item has nothing to do.  Plain launches run after
@@ -58,8 +385,9 @@ __device__ __forceinline__ T* uni(T* p) { return (T*)uni((int64_t)p); }
 template <bool FUSED>
 __device__ __forceinline__ bool item_active(const ProductArgs& a, const TileItem& it, int* sexp) {
   if (it.out < 0) return false;                 // placeholder of a balanced round
-  const LayerState* st = FUSED ? a.probs[it.prob].state : a.state;
-  if (st) {
+  const LayerState* sp = FUSED ? cst(a.probs + it.prob)->state : a.state;
+  if (sp) {
+    const auto* st = cst(sp);
     if (st->done) return false;
     if (it.out == 0) {
       if (FUSED ? (st->d0 && !st->d0_now) : st->d0) return false;
@@ -95,7 +423,7 @@ struct LgkWait {
 // into the next 16-bit buffers with the state's scale, together with FP64
 // partial sums for the decisions; X and X1 never reach memory.
 template <typename T16, int BM, int BK, int WGM, int WGN, int SWZ, int STAGES, bool FUSED>
-__global__ void __launch_bounds__(WGM * WGN * kWave)
+__global__ void __launch_bounds__(WGM * WGN * kWave, BM == 128 ? 2 : 1)
 k_products_split(const ProductArgs a) {
   using S = Split16<T16>;
   using V = typename S::V;
@@ -128,14 +456,15 @@ k_products_split(const ProductArgs a) {
   // on a compact block of tiles and step through k together.
   const int slot = xcd_remap(blockIdx.x, gridDim.x);
   for (int item_id = slot; item_id < a.n_items; item_id += gridDim.x) {
-  const TileItem it = a.items[item_id];
+  const TileItem it = item_at(a.items, item_id);
   int sexp = 0;
   if (!item_active<FUSED>(a, it, &sexp)) continue;
 
   const int j = it.out - 1;
   // operands of this item: the problem's descriptor (fused) or the launch fields
-  const ProblemDesc* pd = FUSED ? a.probs + it.prob : nullptr;
-  const LayerState* fst = FUSED ? pd->state : nullptr;
+  // (through the constant address space: every value of the item stays scalar)
+  const auto* pd = cst(FUSED ? a.probs + it.prob : nullptr);
+  const auto* fst = cst(FUSED ? pd->state : nullptr);
   const int64_t ld = FUSED ? pd->ld : a.ld;
   const int64_t kdim = FUSED ? pd->kdim : a.kdim;
   const int64_t pdim = FUSED ? pd->pdim : a.kdim;
@@ -364,131 +693,42 @@ k_products_split(const ProductArgs a) {
       }
     }
   } else {
-  // Fused epilogue: the layer update of this tile and of its mirror image.
-  // The tile goes through LDS (free after the main loop) in FM rounds: in
-  // round m every wave parks its 32-row fragment strip m, row-major, and the
-  // workgroup then updates those SR rows (direct block, row-major) and their
-  // mirror columns (transposed reads), with coalesced global accesses.
-  // Element (lr, lc) of the upper triangle stands for itself and its mirror,
-  // so the norms weigh it 2 (off the diagonal) or 1 (on it).
+  // the layer update of this tile and of its mirror image, in FM rounds
   constexpr int SR = 32 * WGM;               // tile rows staged per round
-  constexpr int PT = BN + 4;                 // LDS row pitch (floats)
-  constexpr int ITER = SR * BN / (4 * NT);   // float4 groups per thread and round
-  constexpr int G = ITER < 4 ? ITER : 4;
-  static_assert(SR * BN % (4 * NT) == 0 && ITER % G == 0, "whole float4 groups per thread");
-  static_assert(SR * PT * 4 <= STAGES * STAGE * 16, "staging fits in the operand LDS");
+  static_assert(SR * BN * 4 <= STAGES * STAGE * 16, "staging fits in the operand LDS");
   float* T = (float*)lds;
-  const int sig = fst->sigma_cur;
   const bool isx = it.out == 0;
-  const bool upd = isx ? fst->upd_s0 != 0 : true;
-  // ||S - X||_F^2 at the D0 layer, ||S1_j - X1_j||_F^2 once D0 converged
-  const bool diff = isx ? !upd : fst->d0 != 0;
-  const bool need_old = diff || sig < 0;
   const int cur = fst->n & 1;
-  const float* Mr = isx ? pd->s_master : pd->s1m[j][cur ^ 1];
-  float* Mw = isx ? pd->s_master : pd->s1m[j][cur];
-  uint16_t* Hw = (uint16_t*)(isx ? pd->s_hi[fst->s_par ^ 1] : pd->s1_hi[j][cur]);
-  uint16_t* Lw = (uint16_t*)(isx ? pd->s_lo[fst->s_par ^ 1] : pd->s1_lo[j][cur]);
-  const int esplit = isx ? 0 : fst->s1_exp_next[j];
-  typedef uint16_t U4 __attribute__((ext_vector_type(4)));
+  // (opaque: the epilogue's lane values are not carried through the main loop)
+  int etid = tid;
+  asm volatile("" : "+v"(etid));
+  const int elane = etid & (kWave - 1);
+  Epilogue<T16, NT, SR, BN, WTM, BN> ep;
+  ep.flags(fst, it.out, ld);
+  ep.init(etid, &row_a0, &row_b0, pdim, pdim, 1, isx ? pd->s_master : pd->s1m[j][cur ^ 1],
+          isx ? pd->s_master : pd->s1m[j][cur],
+          (uint16_t*)(isx ? pd->s_hi[fst->s_par ^ 1] : pd->s1_hi[j][cur]),
+          (uint16_t*)(isx ? pd->s_lo[fst->s_par ^ 1] : pd->s1_lo[j][cur]));
   double pf = 0.0;
   float pm = 0.0f;
+  // wave (wm, wn) writes rows wm*32 + [0, 32) of T, columns of its fragments; the
+  // rounds share one copy of the code, so fragments are picked by branches
+  auto park = [&](int round) {
 #pragma unroll
-  for (int m = 0; m < FM; ++m) {
-    // park: wave (wm, wn) writes rows wm*32 + [0, 32) of T, columns of its fragments
+    for (int m = 0; m < FM; ++m) {
+      if (round != m) continue;
 #pragma unroll
-    for (int n = 0; n < FN; ++n)
+      for (int n = 0; n < FN; ++n)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = wm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        T[row * PT + wn * WTN + n * 32 + (lane & 31)] = acc[m][n][r] * scale;
-      }
-    __syncthreads();
-    // direct block: T row tr is tile row (tr / 32) * WTM + m * 32 + tr % 32.
-    // Groups of G float4 per thread: the G old-value loads go out together.
-#pragma unroll 1
-    for (int g0 = 0; g0 < ITER; g0 += G) {
-      f32x4 sov[G];
-#pragma unroll
-      for (int i = 0; i < G; ++i) {
-        const int e = (tid + (g0 + i) * NT) * 4;
-        const int tr = e / BN, lc = e % BN;
-        const int lr = (tr >> 5) * WTM + m * 32 + (tr & 31);
-        sov[i] = need_old ? *(const f32x4*)(Mr + (row_a0 + lr) * ld + row_b0 + lc)
-                          : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-      }
-#pragma unroll
-      for (int i = 0; i < G; ++i) {
-        const int e = (tid + (g0 + i) * NT) * 4;
-        const int tr = e / BN, lc = e % BN;
-        const int lr = (tr >> 5) * WTM + m * 32 + (tr & 31);
-        const f32x4 x = *(const f32x4*)(T + tr * PT + lc);
-        const int64_t grow = row_a0 + lr, gcol = row_b0 + lc;
-        const f32x4 so = sov[i];
-        f32x4 sn;
-        uint16_t h[4], l[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          sn[q] = sig > 0 ? x[q] : 2.0f * so[q] - x[q];
-          const int c = lc + q;
-          const double w = diag ? (lr < c ? 2.0 : (lr == c ? 1.0 : 0.0)) : 2.0;
-          const double d = (double)so[q] - (double)x[q];
-          if (diff) pf += w * d * d;
-          if (w > 0.0) pm = fmaxf(pm, fabsf(sn[q]));
-          split_one<T16>(sn[q], esplit, S::kShift, h + q, l + q);
+        for (int r = 0; r < 16; ++r) {
+          const int quad = wm * 8 + 2 * (r >> 2) + (elane >> 5);
+          const int c = wn * WTN + n * 32 + (elane & 31);
+          T[(4 * quad + (r & 3)) * BN + 4 * ((c >> 2) ^ park_swz(quad)) + (c & 3)] =
+              acc[m][n][r] * scale;
         }
-        if (!upd) continue;
-        *(f32x4*)(T + tr * PT + lc) = sn;      // for the mirror pass
-        const int64_t pi = panel_index(grow, gcol, pdim);   // four columns, one panel row
-        if (!diag || lr < lc) {
-          *(f32x4*)(Mw + grow * ld + gcol) = sn;
-          *(U4*)(Hw + pi) = U4{h[0], h[1], h[2], h[3]};
-          *(U4*)(Lw + pi) = U4{l[0], l[1], l[2], l[3]};
-        } else {
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (lr <= lc + q) {
-              Mw[grow * ld + gcol + q] = sn[q];
-              Hw[pi + q] = h[q];
-              Lw[pi + q] = l[q];
-            }
-        }
-      }
     }
-    __syncthreads();
-    // mirror block: row lc of the mirror gets T rows 4 qd .. 4 qd + 3 of column lc
-    if (upd) {
-      for (int e = tid; e < BN * (SR / 4); e += NT) {
-        const int qd = e % (SR / 4), lc = e / (SR / 4);
-        const int tr = 4 * qd;
-        const int lr = (tr >> 5) * WTM + m * 32 + (tr & 31);
-        if (diag && lr >= lc) continue;        // lr + q < lc for some q needs lr < lc
-        f32x4 v;
-        uint16_t h[4], l[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          v[q] = T[(tr + q) * PT + lc];
-          split_one<T16>(v[q], esplit, S::kShift, h + q, l + q);
-        }
-        const int64_t grow = row_b0 + lc, gcol = row_a0 + lr;
-        const int64_t pi = panel_index(grow, gcol, pdim);
-        if (!diag || lr + 3 < lc) {
-          *(f32x4*)(Mw + grow * ld + gcol) = v;
-          *(U4*)(Hw + pi) = U4{h[0], h[1], h[2], h[3]};
-          *(U4*)(Lw + pi) = U4{l[0], l[1], l[2], l[3]};
-        } else {
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (lr + q < lc) {
-              Mw[grow * ld + gcol + q] = v[q];
-              Hw[pi + q] = h[q];
-              Lw[pi + q] = l[q];
-            }
-        }
-      }
-      __syncthreads();
-    }
-  }
+  };
+  ep.template run<FM>(T, pf, pm, park);
   // workgroup partials in a fixed order: butterfly within each wave, then the
   // waves in index order
   __shared__ double red_f[WGM * WGN];
@@ -499,7 +739,7 @@ k_products_split(const ProductArgs a) {
     red_f[wave] = pf;
     red_m[wave] = pm;
   }
-  __syncthreads();
+  lds_barrier();
   if (tid == 0) {
     double f = 0.0;
     float mx = 0.0f;
@@ -516,16 +756,6 @@ k_products_split(const ProductArgs a) {
 }
 
 // ------------------------------------------------------------------ batched pairs
-// Memory that no kernel writes while the product launch runs (the items, the
-// problem descriptors, the layer states, which the decision kernels write
-// between launches), read through the constant address space: workgroup-
-// uniform reads then become scalar loads, which do not queue behind the
-// vector loads in flight and are not counted with them.
-template <typename T>
-__device__ __forceinline__ const __attribute__((address_space(4))) T* cst(const T* p) {
-  return (const __attribute__((address_space(4))) T*)p;
-}
-
 // Fused layer products on items of two 128 x 128 tiles that share a band:
 // (ti, tj) and (ti, tj2) read the same A panels (rows of S, or of S1_j for the
 // second product of a response), (ti, tj) and (ti2, tj) the same B panels.
@@ -557,11 +787,10 @@ k_products_pair(const ProductArgs a) {
   constexpr int LOADS = NARR;                // load rounds per k-tile, one per array
   constexpr int BN = 2 * BM;                 // columns of a pair
   constexpr int SR = 32 * WGM;               // epilogue: tile rows staged per round
-  constexpr int PT = BN + 4;                 // epilogue: LDS row pitch (floats)
   static_assert(RPL == BM, "one load round fills one array");
   static_assert((RPL >> SWZ) % CH == 0, "swizzle must repeat every load round");
   static_assert(kPanelRows % BM == 0 && BK == 32, "tile inside a panel block, two k steps");
-  static_assert(SR * PT * 4 <= STAGES * STAGE * 16, "epilogue staging fits in the operand LDS");
+  static_assert(SR * BN * 4 <= STAGES * STAGE * 16, "epilogue staging fits in the operand LDS");
   extern __shared__ u32x4 lds[];
 
   const int tid = threadIdx.x;
@@ -590,15 +819,7 @@ k_products_pair(const ProductArgs a) {
   // to do; false if there is none.
   auto find = [&](int& id, Ops& o) -> bool {
     for (; id < a.n_items; id += gridDim.x) {
-      // the item as five words (out | prob << 16, ti, tj, ti2, tj2)
-      const auto* w = cst((const uint32_t*)(a.items + id));
-      const uint32_t w0 = w[0];
-      o.it.out = (int16_t)(w0 & 0xffffu);
-      o.it.prob = (int16_t)(w0 >> 16);
-      o.it.ti = (int32_t)w[1];
-      o.it.tj = (int32_t)w[2];
-      o.it.ti2 = (int32_t)w[3];
-      o.it.tj2 = (int32_t)w[4];
+      o.it = item_at(a.items, id);
       if (o.it.out < 0) continue;               // placeholder of a balanced round
       const auto* pd = cst(a.probs + o.it.prob);
       const auto* fst = cst(pd->state);
@@ -816,143 +1037,42 @@ k_products_pair(const ProductArgs a) {
   __builtin_amdgcn_s_waitcnt(0);
   lds_barrier();
 
-  // Fused epilogue, as in k_products_split, over the 256 staged columns of the
-  // pair: column lc is column lc % 128 of tile lc / 128 (at r0_h, c0_h).
+  // Fused epilogue over the 256 staged columns of the pair: column lc is column
+  // lc % 128 of tile lc / 128 (at r0_h, c0_h).
   const float scale = ldexpf(1.0f, -(S::kShift + cur.sexp));
-  const bool diag0 = r0_0 == c0_0, diag1 = r0_1 == c0_1;
-  constexpr int ITER = SR * BN / (4 * NT);   // float4 groups per thread and round
-  constexpr int G = ITER < 4 ? ITER : 4;
-  static_assert(SR * BN % (4 * NT) == 0 && ITER % G == 0, "whole float4 groups per thread");
   float* T = (float*)lds;
-  const int sig = fst->sigma_cur;
   const bool isx = it.out == 0;
-  const bool upd = isx ? fst->upd_s0 != 0 : true;
-  const bool diff = isx ? !upd : fst->d0 != 0;
-  const bool need_old = diff || sig < 0;
   const int cpar = fst->n & 1;
-  const float* Mr = isx ? pd->s_master : pd->s1m[j][cpar ^ 1];
-  float* Mw = isx ? pd->s_master : pd->s1m[j][cpar];
-  uint16_t* Hw = (uint16_t*)(isx ? pd->s_hi[fst->s_par ^ 1] : pd->s1_hi[j][cpar]);
-  uint16_t* Lw = (uint16_t*)(isx ? pd->s_lo[fst->s_par ^ 1] : pd->s1_lo[j][cpar]);
-  const int esplit = isx ? 0 : fst->s1_exp_next[j];
-  typedef uint16_t U4 __attribute__((ext_vector_type(4)));
+  int etid = tid;
+  asm volatile("" : "+v"(etid));
+  const int elane = etid & (kWave - 1);
+  Epilogue<T16, NT, SR, BN, WTM, BM> ep;
+  ep.flags(fst, it.out, ld);
+  const int64_t r0s[2] = {r0_0, r0_1}, c0s[2] = {c0_0, c0_1};
+  ep.init(etid, r0s, c0s, kd, pdim, single ? 1 : 2, isx ? pd->s_master : pd->s1m[j][cpar ^ 1],
+          isx ? pd->s_master : pd->s1m[j][cpar],
+          (uint16_t*)(isx ? pd->s_hi[fst->s_par ^ 1] : pd->s1_hi[j][cpar]),
+          (uint16_t*)(isx ? pd->s_lo[fst->s_par ^ 1] : pd->s1_lo[j][cpar]));
   double pf = 0.0;
   float pm = 0.0f;
+  // wave (wm, wn) writes rows wm*32 + [0, 32) of T, columns of its fragments; the
+  // rounds share one copy of the code, so fragments are picked by branches
+  auto park = [&](int round) {
 #pragma unroll
-  for (int m = 0; m < FM; ++m) {
-    if (live) {
+    for (int m = 0; m < FM; ++m) {
+      if (round != m || !live) continue;
 #pragma unroll
       for (int n = 0; n < FN; ++n)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int row = wm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-          T[row * PT + wn * WTN + n * 32 + (lane & 31)] = acc[m][n][r] * scale;
+          const int quad = wm * 8 + 2 * (r >> 2) + (elane >> 5);
+          const int c = wn * WTN + n * 32 + (elane & 31);
+          T[(4 * quad + (r & 3)) * BN + 4 * ((c >> 2) ^ park_swz(quad)) + (c & 3)] =
+              acc[m][n][r] * scale;
         }
     }
-    lds_barrier();
-    // direct block: T row tr is tile row (tr / 32) * WTM + m * 32 + tr % 32;
-    // a thread's column lc is the same in every group (NT * 4 is a multiple of BN)
-#pragma unroll 1
-    for (int g0 = 0; g0 < ITER; g0 += G) {
-      f32x4 sov[G];
-#pragma unroll
-      for (int i = 0; i < G; ++i) {
-        const int e = (tid + (g0 + i) * NT) * 4;
-        const int tr = e / BN, lc = e % BN;
-        const int h = lc / BM, lcl = lc % BM;
-        const int lr = (tr >> 5) * WTM + m * 32 + (tr & 31);
-        const int64_t grow = (h ? r0_1 : r0_0) + lr, gcol = (h ? c0_1 : c0_0) + lcl;
-        sov[i] = (need_old && !(single && h) && grow < kd && gcol < kd)
-                     ? *(const f32x4*)(Mr + grow * ld + gcol)
-                     : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-      }
-#pragma unroll
-      for (int i = 0; i < G; ++i) {
-        const int e = (tid + (g0 + i) * NT) * 4;
-        const int tr = e / BN, lc = e % BN;
-        const int h = lc / BM, lcl = lc % BM;
-        if (single && h) continue;
-        const int lr = (tr >> 5) * WTM + m * 32 + (tr & 31);
-        const int64_t grow = (h ? r0_1 : r0_0) + lr, gcol = (h ? c0_1 : c0_0) + lcl;
-        // four columns from a multiple of 4: wholly inside kd or wholly past it
-        // (X is zero there, so the partials would gain exact zeros)
-        if (grow >= kd || gcol >= kd) continue;
-        const bool diag = h ? diag1 : diag0;
-        const f32x4 x = *(const f32x4*)(T + tr * PT + lc);
-        const f32x4 so = sov[i];
-        f32x4 sn;
-        uint16_t hh[4], ll[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          sn[q] = sig > 0 ? x[q] : 2.0f * so[q] - x[q];
-          const int c = lcl + q;
-          const double w = diag ? (lr < c ? 2.0 : (lr == c ? 1.0 : 0.0)) : 2.0;
-          const double d = (double)so[q] - (double)x[q];
-          if (diff) pf += w * d * d;
-          if (w > 0.0) pm = fmaxf(pm, fabsf(sn[q]));
-          split_one<T16>(sn[q], esplit, S::kShift, hh + q, ll + q);
-        }
-        if (!upd) continue;
-        // for the mirror pass: the splits, packed hi << 16 | lo, in place of X
-        typedef uint32_t P4 __attribute__((ext_vector_type(4)));
-        *(P4*)(T + tr * PT + lc) = P4{((uint32_t)hh[0] << 16) | ll[0], ((uint32_t)hh[1] << 16) | ll[1],
-                                      ((uint32_t)hh[2] << 16) | ll[2], ((uint32_t)hh[3] << 16) | ll[3]};
-        const int64_t pi = panel_index(grow, gcol, pdim);   // four columns, one panel row
-        if (!diag || lr < lcl) {
-          *(f32x4*)(Mw + grow * ld + gcol) = sn;
-          *(U4*)(Hw + pi) = U4{hh[0], hh[1], hh[2], hh[3]};
-          *(U4*)(Lw + pi) = U4{ll[0], ll[1], ll[2], ll[3]};
-        } else {
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (lr <= lcl + q) {
-              Mw[grow * ld + gcol + q] = sn[q];
-              Hw[pi + q] = hh[q];
-              Lw[pi + q] = ll[q];
-            }
-        }
-      }
-    }
-    lds_barrier();
-    // mirror block: row lc of the mirror gets T rows 4 qd .. 4 qd + 3 of column
-    // lc, in the 16-bit splits only (the next products read whole row panels,
-    // and the direct block left the splits in T);
-    // the FP32 masters are read only on upper tiles, and the outputs are
-    // mirrored when they are copied out
-    if (upd) {
-      for (int e = tid; e < BN * (SR / 4); e += NT) {
-        const int qd = e % (SR / 4), lc = e / (SR / 4);
-        const int h = lc / BM, lcl = lc % BM;
-        if (single && h) continue;
-        const bool diag = h ? diag1 : diag0;
-        const int tr = 4 * qd;
-        const int lr = (tr >> 5) * WTM + m * 32 + (tr & 31);
-        if (diag && lr >= lcl) continue;       // lr + q < lcl for some q needs lr < lcl
-        const int64_t grow = (h ? c0_1 : c0_0) + lcl, gcol = (h ? r0_1 : r0_0) + lr;
-        if (grow >= kd || gcol >= kd) continue;  // T holds splits only where the direct block ran
-        uint16_t hh[4], ll[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const uint32_t u = __builtin_bit_cast(uint32_t, T[(tr + q) * PT + lc]);
-          hh[q] = (uint16_t)(u >> 16);
-          ll[q] = (uint16_t)(u & 0xffffu);
-        }
-        const int64_t pi = panel_index(grow, gcol, pdim);
-        if (!diag || lr + 3 < lcl) {
-          *(U4*)(Hw + pi) = U4{hh[0], hh[1], hh[2], hh[3]};
-          *(U4*)(Lw + pi) = U4{ll[0], ll[1], ll[2], ll[3]};
-        } else {
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (lr + q < lcl) {
-              Hw[pi + q] = hh[q];
-              Lw[pi + q] = ll[q];
-            }
-        }
-      }
-      lds_barrier();
-    }
-  }
+  };
+  ep.template run<FM>(T, pf, pm, park);
   // workgroup partials in a fixed order: butterfly within each wave, then the
   // waves in index order
   __shared__ double red_f[WGM * WGN];

@@ -618,14 +618,73 @@ __global__ void __launch_bounds__(kBlk) k_copy_out(const LayerState* st, int fir
   }
 }
 
+// The split forms keep their masters current on and above the diagonal: a workgroup
+// reads the 64 x 64 block (bi, bj), bi <= bj, by rows and writes it and, through the
+// LDS, its mirror by rows (rows x rows elements, and the columns up to dld of the
+// direct block).
+constexpr int kUpB = 64;
+template <typename D>
+static __device__ void from_upper(const float* src, int64_t ld, D* dst, int64_t dld, int64_t rows,
+                                  int64_t cols, int bi, int bj) {
+  __shared__ float tile[kUpB][kUpB + 1];
+  const int c = threadIdx.x % kUpB, r0 = threadIdx.x / kUpB;
+  const int64_t i0 = (int64_t)bi * kUpB, j0 = (int64_t)bj * kUpB;
+  for (int r = r0; r < kUpB; r += kBlk / kUpB) {
+    const int64_t i = i0 + r, j = j0 + c;
+    if (i < rows && j < cols) {
+      const float v = src[i * ld + j];
+      tile[r][c] = v;
+      if (i <= j) dst[i * dld + j] = (D)v;
+    }
+  }
+  __syncthreads();
+  for (int r = r0; r < kUpB; r += kBlk / kUpB) {
+    const int64_t i = j0 + r, j = i0 + c;                  // element (i, j) below the diagonal
+    if (i < rows && j < rows && i > j) dst[i * dld + j] = (D)tile[c][r];
+  }
+}
+
+__global__ void __launch_bounds__(kBlk) k_copy_out_upper(const LayerState* st, int first,
+                                                        const float* s0, const MatList b0,
+                                                        const MatList b1, int64_t ld,
+                                                        const MatList dsts, int64_t n) {
+  if (blockIdx.y > blockIdx.x) return;
+  const int which = first + (int)blockIdx.z - 1;
+  const float* src = s0;
+  if (which >= 0) {
+    const int L = st->d1[which] && st->d1_layer[which] > 0 ? st->d1_layer[which] - 1 : st->n;
+    src = (const float*)((L & 1) ? b1.p[which] : b0.p[which]);
+  }
+  from_upper(src, ld, (double*)dsts.p[which + 1], n, n, n, blockIdx.y, blockIdx.x);
+}
+
+__global__ void __launch_bounds__(kBlk) k_copy_master_upper(const MatList src, const MatList dst,
+                                                           int64_t rows, int64_t ld) {
+  if (blockIdx.y > blockIdx.x) return;
+  from_upper((const float*)src.p[blockIdx.z], ld, (float*)dst.p[blockIdx.z], ld, rows, ld,
+             blockIdx.y, blockIdx.x);
+}
+
+// masters src[0 .. count) of the split forms, both triangles, to dst
+hipError_t launch_copy_masters(const MatList& src, const MatList& dst, int count, int64_t rows,
+                               int64_t ld, hipStream_t s) {
+  const dim3 grid((unsigned)((ld + kUpB - 1) / kUpB), (unsigned)((rows + kUpB - 1) / kUpB), count);
+  hipLaunchKernelGGL(k_copy_master_upper, grid, dim3(kBlk), 0, s, src, dst, rows, ld);
+  return hipGetLastError();
+}
+
 hipError_t launch_copy_out(dmpt_precision prec, const LayerState* st, int first, int count,
                            const void* s0, const MatList& b0, const MatList& b1, int64_t ld,
                            const MatList& dst, int64_t n, hipStream_t s) {
+  const unsigned nb = (unsigned)((n + kUpB - 1) / kUpB);
   if (prec == DMPT_FP64)
     hipLaunchKernelGGL(k_copy_out<double>, dim3(4096, count), dim3(kBlk), 0, s, st, first,
                        (const double*)s0, b0, b1, ld, dst, n);
-  else
+  else if (prec == DMPT_FP32)
     hipLaunchKernelGGL(k_copy_out<float>, dim3(4096, count), dim3(kBlk), 0, s, st, first,
+                       (const float*)s0, b0, b1, ld, dst, n);
+  else
+    hipLaunchKernelGGL(k_copy_out_upper, dim3(nb, nb, count), dim3(kBlk), 0, s, st, first,
                        (const float*)s0, b0, b1, ld, dst, n);
   return hipGetLastError();
 }
