@@ -197,7 +197,7 @@ __global__ void __launch_bounds__(kBlk) k_b_init(const BatchProblem* P, const Ch
     if (r < b.n && col < b.n) v = c.j < 0 ? ((r == col ? en : 0.0) - H[r * b.n + col]) / w
                                           : -H[r * b.n + col] / w;
     const float f = (float)v;
-    m[q] = f;
+    m[q] = r < b.n && below_in_block(r, col) ? (float)((0.0 - H[col * b.n + r]) / w) : f;
     if (col < b.np) {
       const int64_t pi = panel_index(r, col, b.np);
       split_one<T16>(f, e, t, hi + pi, lo + pi);

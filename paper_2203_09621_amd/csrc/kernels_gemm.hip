@@ -20,6 +20,7 @@
 #include <stdlib.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "layer_common.h"
 #include "split_mfma.h"
@@ -83,7 +84,7 @@ __device__ __forceinline__ TileItem item_at(const TileItem* items, int id) {
 // the splits in place of X, packed hi << 16 | lo, and last the columns are read back
 // as rows of the mirror tile (mirror pass: 16-bit splits alone, since the next
 // products read whole row panels).  The FP32 masters are current on and above the
-// diagonal only; what reads them reads the upper triangle.
+// diagonal and in its 4 x 4 blocks; what reads them reads the upper triangle.
 // Element (lr, lc) of the upper triangle stands for itself and its mirror, so the
 // norms weigh it 2 (off the diagonal) or 1 (on it).
 // What bounds it: instructions and waits.  A workgroup has one or two waves per SIMD,
@@ -192,23 +193,22 @@ struct Epilogue {
     return (r / 32) * WTM + m * 32 + r % 32;
   }
 
-  // old values of a batch (of the elements that exist), of LB batches
-  __device__ __forceinline__ void load(int m, int g, f32x4* so) const {
-    if (!need_old) return;
-    const int r = row(m, g);
-    Glob<const float> p = mr + r * ld;
-#pragma unroll
-    for (int i = 0; i < G; ++i)
-      if (on && r + i * RS + tr0 < rows_ok) so[i] = *(Glob<const f32x4>)(p + i * RS * ld);
+  // The groups of four that the direct pass takes: those that exist and, in a
+  // diagonal tile, those on or above the 4 x 4 blocks of the diagonal.
+  __device__ __forceinline__ bool takes(int lr) const {
+    return on && lr < rows_ok && (!diag || lr <= lcl + 3);
   }
-  template <int LB>
+  // old values of LB batches
+  template <bool FAST, int LB>
   __device__ __forceinline__ void load_step(int m, int g0, f32x4* so) const {
     if (!need_old) return;
 #pragma unroll
     for (int g = 0; g < LB; ++g) {
-      Glob<const float> p = mr + row(m, g0 + g) * ld;
+      const int r = row(m, g0 + g);
+      Glob<const float> p = mr + r * ld;
 #pragma unroll
-      for (int i = 0; i < G; ++i, p += RS * ld) so[g * G + i] = *(Glob<const f32x4>)p;
+      for (int i = 0; i < G; ++i, p += RS * ld)
+        if (FAST || takes(r + i * RS + tr0)) so[g * G + i] = *(Glob<const f32x4>)p;
     }
   }
 
@@ -231,7 +231,7 @@ struct Epilogue {
 #pragma unroll
       for (int i = 0; i < G; ++i) {
         const int lr = r + i * RS + tr0;
-        if (!FAST && !(on && lr < rows_ok)) continue;
+        if (!FAST && !takes(lr)) continue;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const double w = !FAST && diag ? (lr < lcl + q ? 2.0 : (lr == lcl + q ? 1.0 : 0.0)) : 2.0;
@@ -247,39 +247,20 @@ struct Epilogue {
         for (int q = 0; q < 4; ++q) sn[i][q] = 2.0f * so[i][q] - sn[i][q];
     }
 #pragma unroll
-    for (int i = 0; i < G; ++i) {
-      const int lr = r + i * RS + tr0;
-      const bool ok = FAST || (on && lr < rows_ok);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float v = fabsf(sn[i][q]);
-        pm = fmaxf(pm, FAST || (ok && (!diag || lr <= lcl + q)) ? v : 0.0f);
-      }
-    }
-    if (!upd) return;
-#pragma unroll
     for (int i = 0; i < G; ++i, mp += RS * ld) {
-      const int lr = r + i * RS + tr0;
-      if (!FAST && !(on && lr < rows_ok)) continue;
+      if (!FAST && !takes(r + i * RS + tr0)) continue;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) pm = fmaxf(pm, fabsf(sn[i][q]));
+      if (!FAST && !upd) continue;
       uint16_t h[4], l[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         split_one<T16>(sn[i][q], esplit, Split16<T16>::kShift, h + q, l + q);
       *(P4*)tp[i] = P4{((uint32_t)h[0] << 16) | l[0], ((uint32_t)h[1] << 16) | l[1],
                        ((uint32_t)h[2] << 16) | l[2], ((uint32_t)h[3] << 16) | l[3]};
-      if (FAST || !diag || lr <= lcl) {
-        *(Glob<f32x4>)mp = sn[i];
-        *(Glob<U4>)(hp + i * RS * kPanelK) = U4{h[0], h[1], h[2], h[3]};
-        *(Glob<U4>)(lp + i * RS * kPanelK) = U4{l[0], l[1], l[2], l[3]};
-      } else if (lr <= lcl + 3) {
-#pragma unroll
-        for (int q = 1; q < 4; ++q)
-          if (lr <= lcl + q) {
-            mp[q] = sn[i][q];
-            hp[i * RS * kPanelK + q] = h[q];
-            lp[i * RS * kPanelK + q] = l[q];
-          }
-      }
+      *(Glob<f32x4>)mp = sn[i];
+      *(Glob<U4>)(hp + i * RS * kPanelK) = U4{h[0], h[1], h[2], h[3]};
+      *(Glob<U4>)(lp + i * RS * kPanelK) = U4{l[0], l[1], l[2], l[3]};
     }
   }
 
@@ -300,7 +281,7 @@ struct Epilogue {
 #pragma unroll
     for (int i = 0; i < G; ++i) {
       const int c = tid / (SR / 4) + row0 + i * LS;
-      if (!FAST && (c >= rows || lr >= cols || (dg && lr >= c))) continue;
+      if (!FAST && (c >= rows || lr >= cols || (dg && lr + 3 >= c))) continue;
       const int lc = c + t * TILE;
       const float* tp = T + 4 * mq * BN + 4 * ((lc >> 2) ^ f) + (lc & 3);
       uint32_t u[4];
@@ -309,17 +290,8 @@ struct Epilogue {
       const U4 h = U4{(uint16_t)(u[0] >> 16), (uint16_t)(u[1] >> 16), (uint16_t)(u[2] >> 16),
                       (uint16_t)(u[3] >> 16)};
       const U4 l = U4{(uint16_t)u[0], (uint16_t)u[1], (uint16_t)u[2], (uint16_t)u[3]};
-      if (FAST || !dg || lr + 3 < c) {
-        *(Glob<U4>)(hp + i * LS * kPanelK) = h;
-        *(Glob<U4>)(lp + i * LS * kPanelK) = l;
-      } else {
-#pragma unroll
-        for (int q = 0; q < 3; ++q)
-          if (lr + q < c) {
-            hp[i * LS * kPanelK + q] = h[q];
-            lp[i * LS * kPanelK + q] = l[q];
-          }
-      }
+      *(Glob<U4>)(hp + i * LS * kPanelK) = h;
+      *(Glob<U4>)(lp + i * LS * kPanelK) = l;
     }
   }
 
@@ -336,45 +308,64 @@ struct Epilogue {
     static_assert(NG % LB == 0 && ROUNDS % UM == 0, "old values alternate between two sets");
     const bool quick = fast && upd;
     f32x4 so[2][LB * G] = {};
-    if (quick) load_step<LB>(0, 0, so[0]);
+    auto steps = [&](auto quick_c, int m, int p) {
+      constexpr bool FAST = decltype(quick_c)::value;
+#pragma unroll
+      for (int q = 0; q < NS; ++q) {
+        const int cur = (p * NS + q) & 1;
+        const bool last = q + 1 == NS;
+        load_step<FAST, LB>(last && m + 1 < ROUNDS ? m + 1 : m, last ? 0 : (q + 1) * LB,
+                            so[cur ^ 1]);
+#pragma unroll
+        for (int g = 0; g < LB; ++g) direct<FAST>(m, q * LB + g, so[cur] + g * G, T, pf, pm);
+      }
+      lds_barrier();
+      if (FAST || upd) {
+#pragma unroll
+        for (int g = 0; g < MG; ++g) mirror<FAST>(m, g, T);
+        lds_barrier();
+      }
+    };
+    if (quick)
+      load_step<true, LB>(0, 0, so[0]);
+    else
+      load_step<false, LB>(0, 0, so[0]);
 #pragma unroll
     for (int m2 = 0; m2 < ROUNDS; m2 += UM) {
 #pragma unroll
       for (int p = 0; p < UM; ++p) {
-        const int m = m2 + p;
-        park(m);
+        park(m2 + p);
         lds_barrier();
-        if (quick) {
-#pragma unroll
-          for (int q = 0; q < NS; ++q) {
-            const int cur = (p * NS + q) & 1;
-            const bool last = q + 1 == NS;
-            load_step<LB>(last && m + 1 < ROUNDS ? m + 1 : m, last ? 0 : (q + 1) * LB, so[cur ^ 1]);
-#pragma unroll
-            for (int g = 0; g < LB; ++g) direct<true>(m, q * LB + g, so[cur] + g * G, T, pf, pm);
-          }
-          lds_barrier();
-#pragma unroll
-          for (int g = 0; g < MG; ++g) mirror<true>(m, g, T);
-          lds_barrier();
-        } else {
-#pragma unroll 1
-          for (int g = 0; g < NG; ++g) {
-            f32x4 old[G] = {};
-            load(m, g, old);
-            direct<false>(m, g, old, T, pf, pm);
-          }
-          lds_barrier();
-          if (upd) {
-#pragma unroll 1
-            for (int g = 0; g < MG; ++g) mirror<false>(m, g, T);
-            lds_barrier();
-          }
-        }
+        if (quick)
+          steps(std::true_type{}, m2 + p, p);
+        else
+          steps(std::false_type{}, m2 + p, p);
       }
     }
   }
 };
+
+// Fragment v of a wave to the staged strip: rows 4 quad0 + [0, 32), this lane's
+// column c.  A fragment on the diagonal (on_diag) writes the upper half of its 4 x 4
+// diagonal blocks to both places, so that the direct pass takes those blocks whole.
+template <int BN>
+__device__ __forceinline__ void park_fragment(float* T, const f32x16& v, float scale, int quad0,
+                                              int c, int lane, bool on_diag) {
+  const int half = lane >> 5, q4 = (lane & 31) >> 2, k = lane & 3;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int quad = quad0 + 2 * (r >> 2) + half;
+    const float x = v[r] * scale;
+    float* strip = T + 4 * quad * BN + 4 * ((c >> 2) ^ park_swz(quad));
+    if (!on_diag) {
+      strip[(r & 3) * BN + (c & 3)] = x;
+    } else {
+      const bool block = q4 == 2 * (r >> 2) + half;
+      if (!block || (r & 3) <= k) strip[(r & 3) * BN + (c & 3)] = x;
+      if (block && (r & 3) < k) strip[k * BN + (r & 3)] = x;
+    }
+  }
+}
 
 // ------------------------------------------------------------------ split form
 // Resolve the skip flags and the operand scale of one tile item.
@@ -719,13 +710,8 @@ k_products_split(const ProductArgs a) {
       if (round != m) continue;
 #pragma unroll
       for (int n = 0; n < FN; ++n)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int quad = wm * 8 + 2 * (r >> 2) + (elane >> 5);
-          const int c = wn * WTN + n * 32 + (elane & 31);
-          T[(4 * quad + (r & 3)) * BN + 4 * ((c >> 2) ^ park_swz(quad)) + (c & 3)] =
-              acc[m][n][r] * scale;
-        }
+        park_fragment<BN>(T, acc[m][n], scale, wm * 8, wn * WTN + n * 32 + (elane & 31), elane,
+                          diag && wm * WTM + m * 32 == wn * WTN + n * 32);
     }
   };
   ep.template run<FM>(T, pf, pm, park);
@@ -1063,13 +1049,9 @@ k_products_pair(const ProductArgs a) {
       if (round != m || !live) continue;
 #pragma unroll
       for (int n = 0; n < FN; ++n)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int quad = wm * 8 + 2 * (r >> 2) + (elane >> 5);
-          const int c = wn * WTN + n * 32 + (elane & 31);
-          T[(4 * quad + (r & 3)) * BN + 4 * ((c >> 2) ^ park_swz(quad)) + (c & 3)] =
-              acc[m][n][r] * scale;
-        }
+        park_fragment<BN>(T, acc[m][n], scale, wm * 8, wn * WTN + n * 32 + (elane & 31), elane,
+                          (half ? r0_1 == c0_1 : r0_0 == c0_0) &&
+                              wm * WTM + m * 32 == (wn & 1) * WTN + n * 32);
     }
   };
   ep.template run<FM>(T, pf, pm, park);

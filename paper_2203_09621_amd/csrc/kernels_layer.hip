@@ -144,9 +144,11 @@ __global__ void __launch_bounds__(kBlk) k_load(const M* src, M* master, uint16_t
   for (int64_t q = (int64_t)blockIdx.x * kBlk + threadIdx.x; q < total;
        q += (int64_t)gridDim.x * kBlk) {
     const M v = src[q];
-    master[q] = v;
-    if constexpr (SPLIT) {
+    if constexpr (!SPLIT) {
+      master[q] = v;
+    } else {
       const int64_t r = q / ld, c = q - r * ld;
+      master[q] = below_in_block(r, c) ? src[c * ld + r] : v;
       if (c < kdim) {
         const int64_t pi = panel_index(r, c, kdim);
         split_one<T16>((float)v, e, t, hi + pi, lo + pi);
@@ -224,8 +226,10 @@ __global__ void __launch_bounds__(kBlk) k_init_s1(const MatList H1s, int64_t n, 
     double v = 0.0;
     if (H1 && r < n && c < n) v = -H1[r * n + c] / w;
     const M mv = (M)v;
-    s1[q] = mv;
-    if constexpr (SPLIT) {
+    if constexpr (!SPLIT) {
+      s1[q] = mv;
+    } else {
+      s1[q] = H1 && r < n && below_in_block(r, c) ? (M)(-H1[c * n + r] / w) : mv;
       if (c < rows) {
         const int64_t pi = panel_index(r, c, rows);
         split_one<T16>((float)mv, e, t, hi + pi, lo + pi);

@@ -160,6 +160,12 @@ static __device__ __forceinline__ void report_progress(const LayerState* st, int
                      __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// Below the diagonal in its 4 x 4 blocks: there the split forms' masters hold the
+// element above the diagonal (the products' epilogue takes those blocks whole).
+static __device__ __forceinline__ bool below_in_block(int64_t r, int64_t c) {
+  return r > c && (r >> 2) == (c >> 2);
+}
+
 // Split scale: choose e with max|Y| 2^e in [1/16, 1/8), leaving room for the
 // growth of one layer before the next choice.
 static __device__ __forceinline__ int split_exponent(double m) {
