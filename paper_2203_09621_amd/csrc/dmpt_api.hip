@@ -138,21 +138,35 @@ std::vector<TileItem> balanced_items(const std::vector<TileItem>& items, int gri
   return out;
 }
 
-// Tile edge of a single problem's fused layer launch for k responses.  The
-// 256-row launch (one workgroup per CU) needs several work units per CU to
-// balance: with (1 + 2k) T (T + 1) / 2 units of 256-row tiles over the CUs
+// Tile edge and workgroups per CU of a single problem's fused layer launch for k
+// responses.  The 256-row launch (one workgroup per CU) needs several work units per
+// CU to balance: with (1 + 2k) T (T + 1) / 2 units of 256-row tiles over the CUs
 // below 3.4 per CU (N up to about 4096 for one response) the 128-row launch
 // (two workgroups per CU, four times the units) finishes first.  Measured,
 // split FP16, one box: N = 2048, k = 1: 9.0 against 14.5 ms per response;
 // N = 4096, k = 1: 35.0 against 34.8; N = 4096 second order: 64.1 against
-// 73.8; N = 6144: 99.3 against 93.6; N = 8192: 241 against 222.  Contexts
-// that keep adjoint checkpoints stay on 256-row tiles: the adjoint's forward
+// 73.8; N = 6144: 99.3 against 93.6; N = 8192: 241 against 222.
+// The 64-row launch has the shorter items, but reads the LDS twice as often per
+// MFMA: it wins while the CUs have no more than about two of its items each, and a
+// little beyond where the 128-row launch needs a second round (one workgroup per CU
+// while that is enough: given room, the dispatcher stacks them).  Per layer, 64
+// against 128 rows: N = 130, k = 1 (12 items): 26 against 36 us; 512, 3 (144): 40
+// and 52; 1001, 1 (272): 56 and 71 (two per CU: 61); 1001, 3 (544): 71 and 75;
+// 1500, 1 (600): 85 and 90; 1150, 3 (684): 97 and 80; 1300, 3 (924; 264 of 128
+// rows): 122 and 127; 1500, 2 (900; 234): 130 and 101; 1500, 3 (1200): 160 and 142.
+// Contexts that keep adjoint checkpoints stay on 256-row tiles: the adjoint's forward
 // replay runs the same items through the 256-row non-fused kernel.
-int fused_tile(int64_t N, int k, int cus, bool adjoint) {
-  if (adjoint) return 256;
+DirectTile fused_tile(int64_t N, int k, int cus, bool adjoint) {
+  if (adjoint) return {256, 1};
+  auto items = [&](int edge) {                 // per CU
+    const int64_t T = (N + edge - 1) / edge;
+    return (double)(1 + k) * T * (T + 1) / 2 / cus;
+  };
+  const double n64 = items(64);
+  if (n64 <= 2.4 || (n64 <= 4.2 && items(128) > 1.0)) return {64, n64 <= 1.1 ? 1 : 2};
   const int64_t T = (N + 255) / 256;
-  const double per_cu = (double)(1 + 2 * k) * T * (T + 1) / 2 / (cus > 0 ? cus : 256);
-  return per_cu < 3.4 ? 128 : 256;
+  const double units = (double)(1 + 2 * k) * T * (T + 1) / 2 / cus;
+  return units < 3.4 ? DirectTile{128, 2} : DirectTile{256, 1};
 }
 
 // Item positions of the fused launch for k responses on `grid` workgroups,
@@ -206,7 +220,7 @@ struct DevAlloc {
 struct dmpt_ctx {
   dmpt_precision prec;
   int64_t n, nocc, np, ld;
-  int ftile[kMaxK + 1];   // split forms: tile edge of the fused launch for k responses
+  DirectTile ftile[kMaxK + 1];   // split forms: tile of the fused launch for k responses
   DirectTile dtile[kMaxK + 1];   // direct forms: tiling of the products for k responses
   int k_max, max_layers, poll, check_sym;
   hipStream_t stream;
@@ -455,15 +469,14 @@ dmpt_status dmpt_init(dmpt_ctx** out, const double* H0, int64_t N, int64_t Nocc,
     cus = 256;
   for (int k = 1; k <= k_max; ++k) {
     // the launch's tile edge, its tiles and their rounds balanced over its
-    // workgroups (split forms: one workgroup per CU of the 256-row launch, two
-    // of the 128-row one).  Direct forms of a context with checkpoints cover
+    // workgroups.  Direct forms of a context with checkpoints cover
     // all np rows: the adjoint's segment store is not cleared.
     if (split)
       c->ftile[k] = fused_tile(N, k, cus, c->ckpt > 0);
     else
       c->dtile[k] = direct_tile(c->prec, N, 1, k, true);
-    const int edge = split ? c->ftile[k] : c->dtile[k].edge;
-    const int per_cu = split ? (edge == 128 ? 2 : 1) : c->dtile[k].per_cu;
+    const int edge = split ? c->ftile[k].edge : c->dtile[k].edge;
+    const int per_cu = split ? c->ftile[k].per_cu : c->dtile[k].per_cu;
     const int64_t rows = !split && c->ckpt ? c->np : N;
     const int T = (int)((rows + edge - 1) / edge);
     std::vector<TileItem> items = balanced_items(build_items(T, k), per_cu * cus);
@@ -476,8 +489,8 @@ dmpt_status dmpt_init(dmpt_ctx** out, const double* H0, int64_t N, int64_t Nocc,
   if (split) {
     // one slot per item position of every k <= k_max (the plan's length is
     // not monotonic in k: placeholders of balanced rounds)
-    // slots for the larger of the two tilings' plans
-    c->part_cap = fused_slot_capacity((int)((N + 127) / 128), k_max);
+    // slots for the largest of the tilings' plans
+    c->part_cap = fused_slot_capacity((int)((N + 63) / 64), k_max);
     for (int k = 1; k <= k_max; ++k)
       if (c->n_items[k] > c->part_cap) return bail(DMPT_EINVAL, "item plan exceeds slot capacity");
     get((void**)&c->part_f, (size_t)c->part_cap * sizeof(double));
@@ -719,6 +732,7 @@ dmpt_status run_response(dmpt_ctx* c, const double* const* H1, int k1, bool orde
     pa.part_f = c->part_f;
     pa.part_m = c->part_m;
     pa.slot_base = 0;
+    pa.tile = c->ftile[k];
   } else {
     pa.s_hi = c->s_master;
     pa.x = c->x;
@@ -743,7 +757,7 @@ dmpt_status run_response(dmpt_ctx* c, const double* const* H1, int k1, bool orde
       HIPCHK(launch_trace_diag(prec, c->desc, c->tblocks, c->n_tblocks, c->part_tr, s));
       HIPCHK(launch_predecide(c->st, c->part_tr, c->n_tblocks, s));
       if (c->timing) HIPCHK(hipEventRecord(c->pev[2 * (n - 1)], s));
-      HIPCHK(launch_products_fused(prec, c->ftile[k], pa, s));
+      HIPCHK(launch_products_fused(prec, pa, s));
       if (c->timing) HIPCHK(hipEventRecord(c->pev[2 * (n - 1) + 1], s));
       HIPCHK(launch_postdecide(c->st, c->items[k], c->n_items[k], c->part_f, c->part_m, t,
                                c->hprog, s));

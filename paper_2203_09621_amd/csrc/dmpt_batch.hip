@@ -598,7 +598,8 @@ hipError_t launch_products_all(dmpt_batch* b, hipStream_t s) {
     a.items = b->items[0];
     a.n_items = b->n_items[0];
     a.slot_base = 0;
-    e = launch_products_fused(b->prec, 256, a, s);
+    a.tile = DirectTile{256, 1};
+    e = launch_products_fused(b->prec, a, s);
   }
   if (e == hipSuccess && b->n_items[1] > 0) {
     a.items = b->items[1];

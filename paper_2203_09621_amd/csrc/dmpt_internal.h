@@ -212,7 +212,7 @@ void product_items(int T, int mode, TileItem* out);   // T (T + 1) / 2 or T * T 
 // layer n and, in their epilogue, the layer update, the next split and the
 // per-item partial sums; sigma and the update flags come from each problem's
 // state, decided before the launch.
-hipError_t launch_products_fused(dmpt_precision prec, int tile, const ProductArgs& a,
+hipError_t launch_products_fused(dmpt_precision prec, const ProductArgs& a,
                                  hipStream_t s);
 // The same on items of two 128 x 128 tiles that share a row or a column band
 // (TileItem::ti2, tj2), one workgroup per CU: the batch's small-tile class.

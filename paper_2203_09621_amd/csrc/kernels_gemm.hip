@@ -114,7 +114,7 @@ struct Epilogue {
   static constexpr int G = 4;                  // groups of one batch of loads and stores
   static constexpr int NG = ITER / G, MG = MITER / G;
   static_assert(SR == 64 && RS * ITER == SR && LS * MITER == BN, "geometry");
-  static_assert((RS == 4 || RS == 8) && 32 % (RS * G) == 0, "a batch lies in one strip of 32 rows");
+  static_assert(32 % (RS * G) == 0 || WTM == 32, "a batch lies in one strip of 32 rows");
   static_assert(TILE % (LS * G) == 0, "a mirror batch lies in one tile");
   typedef uint16_t U4 __attribute__((ext_vector_type(4)));
   typedef uint32_t P4 __attribute__((ext_vector_type(4)));
@@ -223,7 +223,7 @@ struct Epilogue {
     f32x4 sn[G];
 #pragma unroll
     for (int i = 0; i < G; ++i) {
-      const int quad = RS == 4 ? g * G + i : 2 * (g * G + i) + (tr0 >> 2);
+      const int quad = (RS / 4) * (g * G + i) + (RS == 4 ? 0 : tr0 >> 2);
       tp[i] = tb + i * RS * BN + 4 * (c4 ^ park_swz(quad));
       sn[i] = *(const f32x4*)tp[i];            // X
     }
@@ -302,9 +302,9 @@ struct Epilogue {
   // batch of the 256-row tile; 13 of the 17 us of a round).
   template <int ROUNDS, typename Park>
   __device__ __forceinline__ void run(float* T, double& pf, float& pm, Park park) const {
-    constexpr int LB = NG > 2 ? 1 : 2;         // batches loaded together
+    constexpr int LB = NG == 2 ? 2 : 1;        // batches loaded together
     constexpr int NS = NG / LB;                // such steps per round
-    constexpr int UM = NS % 2 ? 2 : 1;         // rounds after which the sets are in place again
+    constexpr int UM = NS % 2 && ROUNDS > 1 ? 2 : 1;   // rounds after which the sets are in place again
     static_assert(NG % LB == 0 && ROUNDS % UM == 0, "old values alternate between two sets");
     const bool quick = fast && upd;
     f32x4 so[2][LB * G] = {};
@@ -414,7 +414,7 @@ struct LgkWait {
 // into the next 16-bit buffers with the state's scale, together with FP64
 // partial sums for the decisions; X and X1 never reach memory.
 template <typename T16, int BM, int BK, int WGM, int WGN, int SWZ, int STAGES, bool FUSED>
-__global__ void __launch_bounds__(WGM * WGN * kWave, BM == 128 ? 2 : 1)
+__global__ void __launch_bounds__(WGM * WGN * kWave, BM == 256 ? 1 : 2)
 k_products_split(const ProductArgs a) {
   using S = Split16<T16>;
   using V = typename S::V;
@@ -514,7 +514,7 @@ k_products_split(const ProductArgs a) {
   // i, so every load round adds only a wave-uniform offset.
   static_assert(kPanelRows % BM == 0 && BK == kPanelK, "tile inside a panel block");
   static_assert((RPL >> SWZ) % CH == 0, "swizzle must repeat every load round");
-  static_assert(STAGES == 2 && BK == 32, "two stages of two 16-wide k steps");
+  static_assert((STAGES & (STAGES - 1)) == 0 && BK == 32, "stages by mask, two 16-wide k steps");
   const int64_t kblocks = uni(pdim / kPanelK);
   const int csrc = lsl ^ ((lrow >> SWZ) & (CH - 1));
   const int voff = lrow * kPanelK + csrc * 8;
@@ -522,7 +522,7 @@ k_products_split(const ProductArgs a) {
                            (row_a0 % kPanelRows) * kPanelK);
   const int64_t offb = uni((row_b0 / kPanelRows) * kblocks * (kPanelRows * kPanelK) +
                            (row_b0 % kPanelRows) * kPanelK);
-  // Tile t of the concatenated k range goes to stage t % 2.  Past the end the
+  // Tile t of the concatenated k range goes to stage t % STAGES.  Past the end the
   // last tile is fetched again (into a stage nobody reads any more), so the
   // loop body has no branches.  One load round moves RPL rows of one array.
   struct Fetch { const uint16_t* q[4]; u32x4* dst; };
@@ -534,7 +534,7 @@ k_products_split(const ProductArgs a) {
 #pragma unroll
     for (int r = 0; r < 4; ++r)
       f.q[r] = (p == 0 ? Q0[r] : (p == 1 ? Q1[r] : Q2[r])) + (r < 2 ? offa : offb) + kofs;
-    f.dst = lds + (t0 & 1) * STAGE;
+    f.dst = lds + (t0 & (STAGES - 1)) * STAGE;
     return f;
   };
   auto issue_round = [&](const Fetch& f, int i) {
@@ -618,22 +618,26 @@ k_products_split(const ProductArgs a) {
   // one barrier per k-tile sits between its two k steps: by then every wave
   // holds the second step's fragments (its stage may be refilled) and every
   // wave's loads of the next tile have landed (it may be read).
-  static_assert(NM >= NF, "at least one MFMA per LDS read");
   Frag f0, f1;
-  issue(0);
-  issue(1);
-  __builtin_amdgcn_s_waitcnt(VmWait<LOADS>::imm);
+#pragma unroll
+  for (int t0 = 0; t0 < STAGES; ++t0) issue(t0);
+  __builtin_amdgcn_s_waitcnt(VmWait<(STAGES - 1) * LOADS>::imm);
   __syncthreads();
   read(0, 0, f0);
   auto body = [&](int t) {
     // f0 was read during the previous k step and has landed: wait for it
     // before more reads are queued (the counter cannot express "all but NF")
     __builtin_amdgcn_s_waitcnt(LgkWait<0>::imm);
-    step(f0, f1, t & 1, 1, nullptr);
-    const Fetch fe = prep(t + 2);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    step(f1, f0, (t + 1) & 1, 0, &fe);
+    step(f0, f1, t & (STAGES - 1), 1, nullptr);
+    const Fetch fe = prep(t + STAGES);
+    if constexpr (STAGES == 2) {
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+    } else {
+      __builtin_amdgcn_s_waitcnt(VmWait<(STAGES - 2) * LOADS>::imm);
+      lds_barrier();
+    }
+    step(f1, f0, (t + 1) & (STAGES - 1), 0, &fe);
   };
   // second-order items: the S1_0 S1_0 product (scale 2^(t + 2 e1)) is brought
   // to the scale of S S2 before the other two are accumulated
@@ -1431,12 +1435,26 @@ static hipError_t launch_split(const ProductArgs& a, hipStream_t s) {
   return launch_split_cfg<T16, kPanelK, kSplitWGM, kSplitWGN, 2, 2, FUSED>(a, s);
 }
 
-template <typename T16>
+template <typename T16, int BM, int STAGES, int PER_CU>
 static hipError_t launch_split_small(const ProductArgs& a, hipStream_t s) {
-  // 128 x 128 tiles, 4 waves of 64 x 64, two workgroups per CU
-  constexpr size_t lds = (size_t)2 * (4 * 128) * (kPanelK / 8) * 16;
-  return launch_one(k_products_split<T16, 128, kPanelK, 2, 2, 2, 2, true>, 4 * kWave, lds, 2, a,
-                    s);
+  // 128 x 128 tiles in two stages (four, with one workgroup per CU, changed nothing:
+  // a k-tile waits for its LDS reads and MFMAs, not for its loads) or 64 x 64 tiles
+  // in four, 4 waves of a quarter each
+  // (as much LDS as leaves no room for more workgroups than that: given room, the
+  // dispatcher stacks them on some CUs and leaves others idle)
+  constexpr size_t need = (size_t)STAGES * (4 * BM) * (kPanelK / 8) * 16;
+  constexpr size_t lds = std::max(need, (size_t)160 * 1024 / (PER_CU + 1) + 1024);
+  static_assert(PER_CU * lds <= 160 * 1024 - 256, "LDS of one CU");
+  return launch_one(k_products_split<T16, BM, kPanelK, 2, 2, 2, STAGES, true>, 4 * kWave, lds,
+                    PER_CU, a, s);
+}
+
+template <typename T16>
+static hipError_t launch_split_fused(const ProductArgs& a, hipStream_t s) {
+  if (a.tile.edge == 256) return launch_split<T16, true>(a, s);
+  if (a.tile.edge == 128) return launch_split_small<T16, 128, 2, 2>(a, s);
+  return a.tile.per_cu == 1 ? launch_split_small<T16, 64, 4, 1>(a, s)
+                            : launch_split_small<T16, 64, 4, 2>(a, s);
 }
 
 template <typename T16>
@@ -1483,14 +1501,14 @@ hipError_t launch_products_pair(dmpt_precision prec, const ProductArgs& a, hipSt
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_products_fused(dmpt_precision prec, int tile, const ProductArgs& a,
+hipError_t launch_products_fused(dmpt_precision prec, const ProductArgs& a,
                                  hipStream_t s) {
-  if (!a.probs || !a.part_f || !a.part_m || (tile != 128 && tile != 256))
+  if (!a.probs || !a.part_f || !a.part_m || (a.tile.edge != 64 && a.tile.edge != 128 && a.tile.edge != 256))
     return hipErrorInvalidValue;
   if (prec == DMPT_SPLIT_FP16)
-    return tile == 128 ? launch_split_small<_Float16>(a, s) : launch_split<_Float16, true>(a, s);
+    return launch_split_fused<_Float16>(a, s);
   if (prec == DMPT_SPLIT_BF16)
-    return tile == 128 ? launch_split_small<__bf16>(a, s) : launch_split<__bf16, true>(a, s);
+    return launch_split_fused<__bf16>(a, s);
   return hipErrorInvalidValue;
 }
 

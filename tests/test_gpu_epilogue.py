@@ -38,3 +38,26 @@ def test_outputs_do_not_depend_on_the_tile(precision, h1):
             assert torch.equal(a, c), (p.N, "pairs")
             assert torch.equal(a, a.T), p.N
             assert np.isfinite(a.cpu().numpy()).all()
+
+
+# single problems: 64-row tiles with one and with two workgroups per CU, 128-row tiles
+# (two sizes beside each change of the rule), against the batch's pairs
+@pytest.mark.parametrize("n,k", [(129, 1), (704, 3), (705, 3), (1024, 1), (1025, 1), (1024, 3),
+                                 (1100, 3), (1290, 3), (1536, 1), (1537, 1)])
+def test_single_problem_tiles_agree(n, k):
+    import torch
+
+    import paper_2203_09621_amd as dm
+    from workloads import dense_gapped_problem
+
+    p = dense_gapped_problem(n, n // 2, 0.8, 500 + n, h1="diag", k=k)
+    H0, H1 = torch.from_numpy(p.H0).cuda(), [torch.from_numpy(h).cuda() for h in p.H1]
+    b = dm.dmpt_batch_init([n], [p.nocc], [k], precision="split_fp16", tile_threshold=100000)
+    try:
+        Q0, Q1, _, _ = dm.dmpt_batch_response(b, [H0], [H1])
+    finally:
+        dm.dmpt_batch_destroy(b)
+    P0, P1s, st = dm.solve(H0, H1, p.nocc, precision="split_fp16")
+    assert st["converged"]
+    for x, y in zip([P0, *P1s], [Q0[0], *Q1[0]]):
+        assert torch.equal(x, y) and torch.equal(x, x.T)
