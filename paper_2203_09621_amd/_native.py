@@ -8,7 +8,10 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
+from array import array
 from ctypes import POINTER, byref, c_char_p, c_double, c_int8, c_int32, c_int64, c_void_p
+from operator import attrgetter
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libdmpt.so")
@@ -68,6 +71,17 @@ class DmptProblemStats(ctypes.Structure):
         return {"layers": self.layers, "d0_layer": self.d0_layer,
                 "converged": bool(self.converged), "k": k, "d1_layer": list(self.d1_layer[:k]),
                 "idem0": self.idem0, "idem1": list(self.idem1[:k])}
+
+
+_PROBLEM_STATS = struct.Struct("=8i4d")      # DmptProblemStats
+assert _PROBLEM_STATS.size == ctypes.sizeof(DmptProblemStats)
+
+
+def _problem_stats(st) -> list:
+    """[x.as_dict() for x in st], unpacked from the array's bytes."""
+    return [{"layers": n, "d0_layer": d0, "converged": c != 0, "k": k,
+             "d1_layer": [a, b, d][:k], "idem0": i0, "idem1": [i1, i2, i3][:k]}
+            for n, d0, c, k, a, b, d, _, i0, i1, i2, i3 in _PROBLEM_STATS.iter_unpack(st)]
 
 
 # induced-field callback of dmpt_cpscf: (user, P1, G, stream)
@@ -182,6 +196,23 @@ def _dev(t, name):
     if t.dtype != torch.float64 or not t.is_contiguous() or t.dim() != 2 or t.shape[0] != t.shape[1]:
         raise TypeError(f"{name} must be a contiguous square float64 tensor")
     return c_void_p(t.data_ptr())
+
+
+_DTYPE, _IS_CUDA, _SHAPE = attrgetter("dtype"), attrgetter("is_cuda"), attrgetter("shape")
+
+
+def _devs(ts, name):
+    """The pointer array of a list of tensors with the checks of _dev on each.  Whole
+    lists go through C-level accessors (a batch passes tens of thousands of tensors);
+    a list that fails is taken one by one, for the error of its first bad entry."""
+    torch = _torch()
+    T = torch.Tensor
+    ok = (all(issubclass(c, T) for c in set(map(type, ts)))
+          and set(map(_DTYPE, ts)) <= {torch.float64}
+          and all(map(_IS_CUDA, ts)) and all(map(T.is_contiguous, ts))
+          and all(len(s) == 2 and s[0] == s[1] for s in set(map(_SHAPE, ts))))
+    ptrs = list(map(T.data_ptr, ts)) if ok else [_dev(t, name).value for t in ts]
+    return (c_void_p * len(ptrs)).from_buffer(array("Q", ptrs)) if ptrs else (c_void_p * 0)()
 
 
 def _stream(stream):
@@ -498,11 +529,9 @@ def dmpt_batch_response(batch: c_void_p, H0s, H1s, P0s=None, P1s=None):
     st = (DmptProblemStats * count)()
     ms = c_double(0.0)
     status = LIB.dmpt_batch_response(
-        batch, (c_void_p * count)(*[_dev(h, "H0").value for h in H0s]),
-        (c_void_p * len(flat_h1))(*[_dev(h, "H1").value for h in flat_h1]),
-        (c_void_p * count)(*[_dev(p, "P0").value for p in P0s]),
-        (c_void_p * len(flat_p1))(*[_dev(p, "P1").value for p in flat_p1]), st, byref(ms))
-    stats = [x.as_dict() for x in st]
+        batch, _devs(H0s, "H0"), _devs(flat_h1, "H1"), _devs(P0s, "P0"), _devs(flat_p1, "P1"),
+        st, byref(ms))
+    stats = _problem_stats(st)
     _check(status, {"problems": stats})
     return P0s, P1s, stats, ms.value
 

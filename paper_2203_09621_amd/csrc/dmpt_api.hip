@@ -209,6 +209,46 @@ struct DevAlloc {
     if (e == hipSuccess) ptrs.push_back(*p);
     return e;
   }
+  // Buffers asked for one by one and allocated by commit(): those of kLow bytes and
+  // more in chunks of up to kChunk, each with as many as fit.  From 2 MB on every
+  // hipMalloc maps and every hipFree unmaps memory, at 40 to 100 us each: set-up and
+  // release of a context for N = 1001 and three responses, with 24 such buffers, took
+  // 3.3 ms with a call per buffer and takes 0.9 ms.  Smaller buffers come out of blocks
+  // that the runtime keeps (4 us each).
+  static constexpr size_t kLow = (size_t)2 << 20, kChunk = (size_t)64 << 20;
+  struct Want {
+    void** p;
+    size_t bytes;
+  };
+  std::vector<Want> wants;
+  void want(void** p, size_t bytes) {
+    *p = nullptr;
+    if (bytes) wants.push_back({p, bytes});
+  }
+  hipError_t commit() {
+    hipError_t e = hipSuccess;
+    std::vector<Want> large;
+    for (const Want& w : wants) {
+      if (w.bytes >= kLow)
+        large.push_back(w);
+      else if (e == hipSuccess)
+        e = get(w.p, w.bytes);
+    }
+    wants.clear();
+    auto up = [](size_t x) { return (x + kLow - 1) / kLow * kLow; };
+    for (size_t i = 0; i < large.size() && e == hipSuccess;) {
+      size_t n = i, total = 0;
+      for (; n < large.size() && (n == i || up(total) + large[n].bytes <= kChunk); ++n)
+        total = up(total) + large[n].bytes;
+      char* base = nullptr;
+      e = get((void**)&base, total);
+      for (size_t ofs = 0; i < n && e == hipSuccess; ++i) {
+        *large[i].p = base + ofs;
+        ofs = up(ofs + large[i].bytes);
+      }
+    }
+    return e;
+  }
   void release() {
     for (void* p : ptrs) (void)hipFree(p);
     ptrs.clear();
@@ -245,7 +285,7 @@ struct dmpt_ctx {
   int32_t* dflag;
   TileItem* items[kMaxK + 1];
   int n_items[kMaxK + 1];
-  LayerState* hstate; // pinned host copy
+  LayerState* hstate; // pinned host copy, the start of one block with hflag and hprog
   int32_t* hflag;     // pinned host flags
   int32_t* hprog;     // pinned: 2 n + done of the response's last finished layer n
   bool in_flight;     // kernels that write hprog may still run
@@ -284,8 +324,6 @@ void ctx_free(dmpt_ctx* c) {
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   c->mem.release();
   if (c->hstate) (void)hipHostFree(c->hstate);
-  if (c->hflag) (void)hipHostFree(c->hflag);
-  if (c->hprog) (void)hipHostFree(c->hprog);
   if (c->ev0) (void)hipEventDestroy(c->ev0);
   if (c->ev1) (void)hipEventDestroy(c->ev1);
   for (int i = 0; i < 2 * kMaxLayers; ++i)
@@ -396,8 +434,20 @@ dmpt_status dmpt_init(dmpt_ctx** out, const double* H0, int64_t N, int64_t Nocc,
   const size_t eb = elem_bytes(c->prec);
   const size_t mat = (size_t)c->np * c->ld;
   hipError_t e = hipSuccess;
-  auto get = [&](void** p, size_t bytes) {
-    if (e == hipSuccess) e = c->mem.get(p, bytes);
+  auto get = [&](void** p, size_t bytes) { c->mem.want(p, bytes); };
+  // tables the host fills, uploaded together
+  std::vector<char> stage;
+  struct Table {
+    void** p;
+    size_t ofs;
+  };
+  std::vector<Table> tables;
+  auto table = [&](void** p, const void* src, size_t bytes) {
+    const size_t ofs = (stage.size() + 63) / 64 * 64;
+    stage.resize(ofs + bytes);
+    if (src) memcpy(stage.data() + ofs, src, bytes);
+    tables.push_back({p, ofs});
+    return ofs;
   };
   get((void**)&c->st, sizeof(LayerState));
   get(&c->s_init, mat * eb);
@@ -450,16 +500,7 @@ dmpt_status dmpt_init(dmpt_ctx** out, const double* H0, int64_t N, int64_t Nocc,
       std::vector<TileItem> items =
           build_items_all_tiles((int)(c->np / c->adj_tile[k].edge), 1 + 2 * k);
       c->adj_n_items[k] = (int)items.size();
-      get((void**)&c->adj_items[k], items.size() * sizeof(TileItem));
-      if (e == hipSuccess)
-        e = hipMemcpy(c->adj_items[k], items.data(), items.size() * sizeof(TileItem),
-                      hipMemcpyHostToDevice);
-    }
-    // outputs of the adjoint products leave the pad columns untouched
-    if (e == hipSuccess) e = hipMemset(c->t2, 0, mat * eb);
-    for (int j = 0; j < k_max && j < 3 && e == hipSuccess; ++j) {
-      e = hipMemset(c->t1[j], 0, mat * eb);
-      if (e == hipSuccess) e = hipMemset(c->t3[j], 0, mat * eb);
+      table((void**)&c->adj_items[k], items.data(), items.size() * sizeof(TileItem));
     }
   }
   int cus = 0, dev = 0;
@@ -481,11 +522,9 @@ dmpt_status dmpt_init(dmpt_ctx** out, const double* H0, int64_t N, int64_t Nocc,
     const int T = (int)((rows + edge - 1) / edge);
     std::vector<TileItem> items = balanced_items(build_items(T, k), per_cu * cus);
     c->n_items[k] = (int)items.size();
-    get((void**)&c->items[k], items.size() * sizeof(TileItem));
-    if (e == hipSuccess)
-      e = hipMemcpy(c->items[k], items.data(), items.size() * sizeof(TileItem),
-                    hipMemcpyHostToDevice);
+    table((void**)&c->items[k], items.data(), items.size() * sizeof(TileItem));
   }
+  size_t desc_ofs = 0;
   if (split) {
     // one slot per item position of every k <= k_max (the plan's length is
     // not monotonic in k: placeholders of balanced rounds)
@@ -495,16 +534,21 @@ dmpt_status dmpt_init(dmpt_ctx** out, const double* H0, int64_t N, int64_t Nocc,
       if (c->n_items[k] > c->part_cap) return bail(DMPT_EINVAL, "item plan exceeds slot capacity");
     get((void**)&c->part_f, (size_t)c->part_cap * sizeof(double));
     get((void**)&c->part_m, (size_t)c->part_cap * sizeof(double));
-    get((void**)&c->desc, sizeof(ProblemDesc));
+    desc_ofs = table((void**)&c->desc, nullptr, sizeof(ProblemDesc));
     c->n_tblocks = (int)((N + 31) / 32);
-    get((void**)&c->tblocks, (size_t)c->n_tblocks * sizeof(TraceBlock));
+    std::vector<TraceBlock> tb(c->n_tblocks);
+    for (int b = 0; b < c->n_tblocks; ++b) tb[b] = TraceBlock{0, b};
+    table((void**)&c->tblocks, tb.data(), tb.size() * sizeof(TraceBlock));
     get((void**)&c->part_tr, (size_t)c->n_tblocks * sizeof(double));
-    if (e == hipSuccess) {
-      std::vector<TraceBlock> tb(c->n_tblocks);
-      for (int b = 0; b < c->n_tblocks; ++b) tb[b] = TraceBlock{0, b};
-      e = hipMemcpy(c->tblocks, tb.data(), tb.size() * sizeof(TraceBlock), hipMemcpyHostToDevice);
-    }
-    if (e == hipSuccess) {
+  }
+  char* tab = nullptr;
+  get((void**)&tab, stage.size());
+  e = c->mem.commit();
+  if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation)
+    return bail(DMPT_ENOMEM, "device allocation failed");
+  if (e == hipSuccess) {
+    for (const Table& t : tables) *t.p = tab + t.ofs;
+    if (split) {
       ProblemDesc d;
       memset(&d, 0, sizeof(d));
       for (int b = 0; b < 2; ++b) {
@@ -521,11 +565,18 @@ dmpt_status dmpt_init(dmpt_ctx** out, const double* H0, int64_t N, int64_t Nocc,
       d.ld = c->ld;
       d.kdim = (N + kPanelK - 1) / kPanelK * kPanelK;
       d.pdim = c->np;
-      e = hipMemcpy(c->desc, &d, sizeof(d), hipMemcpyHostToDevice);
+      memcpy(stage.data() + desc_ofs, &d, sizeof(d));
+    }
+    e = hipMemcpy(tab, stage.data(), stage.size(), hipMemcpyHostToDevice);
+  }
+  // outputs of the adjoint products leave the pad columns untouched
+  if (e == hipSuccess && c->ckpt) {
+    e = hipMemset(c->t2, 0, mat * eb);
+    for (int j = 0; j < k_max && j < 3 && e == hipSuccess; ++j) {
+      e = hipMemset(c->t1[j], 0, mat * eb);
+      if (e == hipSuccess) e = hipMemset(c->t3[j], 0, mat * eb);
     }
   }
-  if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation)
-    return bail(DMPT_ENOMEM, "device allocation failed");
   // the products never write the pad columns of X and X1: they must start at zero
   if (e == hipSuccess) e = hipMemset(c->st, 0, sizeof(LayerState));
   if (e == hipSuccess && c->x) e = hipMemset(c->x, 0, mat * eb);
@@ -534,10 +585,14 @@ dmpt_status dmpt_init(dmpt_ctx** out, const double* H0, int64_t N, int64_t Nocc,
     if (e == hipSuccess) e = hipMemset(c->s1buf[j][1], 0, mat * eb);
   }
   if (e != hipSuccess) return bail(DMPT_EHIP, std::string("allocation: ") + hipGetErrorString(e));
-  if (hipHostMalloc((void**)&c->hstate, sizeof(LayerState), 0) != hipSuccess ||
-      hipHostMalloc((void**)&c->hflag, 16 * sizeof(int32_t), 0) != hipSuccess ||
-      hipHostMalloc((void**)&c->hprog, sizeof(int32_t), hipHostMallocCoherent) != hipSuccess)
+  // one pinned block: the state's copy, flags, progress (coherent: kernels write it)
+  constexpr size_t kFlagOfs = (sizeof(LayerState) + 127) / 128 * 128;
+  char* pinned = nullptr;
+  if (hipHostMalloc((void**)&pinned, kFlagOfs + 256, hipHostMallocCoherent) != hipSuccess)
     return bail(DMPT_ENOMEM, "pinned host allocation failed");
+  c->hstate = (LayerState*)pinned;
+  c->hflag = (int32_t*)(pinned + kFlagOfs);
+  c->hprog = (int32_t*)(pinned + kFlagOfs + 128);
   if (hipEventCreate(&c->ev0) != hipSuccess || hipEventCreate(&c->ev1) != hipSuccess)
     return bail(DMPT_EHIP, "event creation failed");
   c->timing = opt.timing;
