@@ -139,13 +139,15 @@ std::vector<TileItem> balanced_items(const std::vector<TileItem>& items, int gri
 }
 
 // Tile edge and workgroups per CU of a single problem's fused layer launch for k
-// responses.  The 256-row launch (one workgroup per CU) needs several work units per
-// CU to balance: with (1 + 2k) T (T + 1) / 2 units of 256-row tiles over the CUs
-// below 3.4 per CU (N up to about 4096 for one response) the 128-row launch
-// (two workgroups per CU, four times the units) finishes first.  Measured,
-// split FP16, one box: N = 2048, k = 1: 9.0 against 14.5 ms per response;
-// N = 4096, k = 1: 35.0 against 34.8; N = 4096 second order: 64.1 against
-// 73.8; N = 6144: 99.3 against 93.6; N = 8192: 241 against 222.
+// responses.  The 256-row launch (one workgroup per CU) takes as long as its fullest
+// CU: M units, a tile of X being one and a response tile, which no two CUs share, two.
+// The 128-row launch (two workgroups per CU) has quarter units, which even out, and
+// needs about 1 / 3.05 of a 256-row unit's time for each of the U it has per CU.
+// Measured, split FP16, us per layer, 256 against 128 rows: N = 4096: k = 1 (M = 2, U
+// = 6.2) 665 and 680, k = 2 (4, 10.3) 1167 and 1039, k = 3 (4, 14.4) 1301 and 1437;
+// N = 3500, k = 2 (3, 7.9) 816 and 664; N = 4600, k = 1 (3, 7.8) 1062 and 859;
+// N = 5200, k = 1 (3, 10.1) 1193 and 1339, k = 2 (5, 16.8) 1940 and 2088; N = 6144,
+// k = 1 (4, 13.8) 1857 and 1972; N = 3000, k = 1 (2, 3.5) 377 and 306.
 // The 64-row launch has the shorter items, but reads the LDS twice as often per
 // MFMA: it wins while the CUs have no more than about two of its items each, and a
 // little beyond where the 128-row launch needs a second round (one workgroup per CU
@@ -164,9 +166,11 @@ DirectTile fused_tile(int64_t N, int k, int cus, bool adjoint) {
   };
   const double n64 = items(64);
   if (n64 <= 2.4 || (n64 <= 4.2 && items(128) > 1.0)) return {64, n64 <= 1.1 ? 1 : 2};
-  const int64_t T = (N + 255) / 256;
-  const double units = (double)(1 + 2 * k) * T * (T + 1) / 2 / cus;
-  return units < 3.4 ? DirectTile{128, 2} : DirectTile{256, 1};
+  const int64_t T = (N + 255) / 256, t = T * (T + 1) / 2;
+  int64_t M = 1;
+  while (k * t > cus * (M / 2) || (1 + 2 * k) * t > cus * M) ++M;
+  const double U = items(128) * (1 + 2 * k) / (1 + k);
+  return U < 3.05 * M ? DirectTile{128, 2} : DirectTile{256, 1};
 }
 
 // Item positions of the fused launch for k responses on `grid` workgroups,
