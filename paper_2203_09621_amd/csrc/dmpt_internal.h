@@ -161,7 +161,7 @@ struct ProductArgs {
   int32_t plain_accum;       // FP32 direct form: nonzero runs one accumulator over the whole
                              // k range instead of blocked sums (faster, less accurate; the
                              // adjoint's reverse products, whose error the forward dominates)
-  DirectTile tile;           // direct forms: tiling of `items` (direct_tile)
+  DirectTile tile;           // tiling of `items`: direct forms direct_tile, fused split forms fused_tile
   int64_t kext;              // direct forms: k extent of the products, N rounded up to 64 (the
                              // operands are zero from N on, so every k past N adds exact zeros)
 };
