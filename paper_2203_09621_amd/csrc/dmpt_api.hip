@@ -293,6 +293,7 @@ struct dmpt_ctx {
   int32_t* hflag;     // pinned host flags
   int32_t* hprog;     // pinned: 2 n + done of the response's last finished layer n
   bool in_flight;     // kernels that write hprog may still run
+  bool soiled;        // direct forms: the last response did not end well (run_response)
   hipEvent_t ev0, ev1;
   int timing;
   hipEvent_t pev[2 * kMaxLayers];  // per-layer product launch bracket (timing on)
@@ -692,6 +693,7 @@ dmpt_status finish_response(dmpt_ctx* c, int k, bool order2, double* P0, Out slo
   }
   if (h.error) return fail((dmpt_status)h.error, "non-finite value or split overflow in a layer");
   if (!h.converged) return fail(DMPT_ENOCONV, "layer cap reached before every D1 test fired");
+  c->soiled = false;
   c->last_k = order2 ? 0 : k;          // the adjoint covers first-order responses
   return DMPT_OK;
 }
@@ -758,6 +760,19 @@ dmpt_status run_response(dmpt_ctx* c, const double* const* H1, int k1, bool orde
                         s));
 
   const size_t mbytes = (size_t)elems * elem_bytes(prec);
+  // The direct launches cover N rounded up to the tile edge of k responses; the update
+  // and the k range of the products reach further, where X and the S1 hold the zeros of
+  // dmpt_init.  Every product of zero rows is zero unless an operand is not finite, so
+  // after a response that failed (or was capped, with norms that no test looked at) the
+  // zeros are restored: one with other tiles would not write over what it left.
+  // (S and the first S1 buffers were written in full above.)
+  if (!split) {
+    if (c->soiled) {
+      HIPCHK(hipMemsetAsync(c->x, 0, mbytes, s));
+      for (int j = 0; j < c->k_max; ++j) HIPCHK(hipMemsetAsync(c->s1buf[j][1], 0, mbytes, s));
+    }
+    c->soiled = true;                          // until this response has converged
+  }
   auto save_ckpt = [&](int layer) -> hipError_t {
     const int slot = layer / c->ckpt;
     if (slot >= c->nslots) return hipSuccess;
