@@ -37,7 +37,9 @@ __global__ void __launch_bounds__(kBlk) k_scaled_identity(M* z, double c, int64_
 // product is not zero, so this is what the product kernels give, bit for bit (adding
 // 0 makes a zero term's sign theirs), at the cost of a pass over memory: at N = 4096
 // in FP64 0.05 ms in place of 2.0 + 1.3 ms.  A workgroup reads a 32 x 32 tile of the
-// lower triangle by rows and writes it and, through the LDS, its mirror by rows.
+// lower triangle by rows and writes it and, through the LDS, its mirror by rows.  The
+// upper triangle enters with a factor of zero, as it did in the dot products: what is
+// not finite there is NaN in X.
 constexpr int kMirTile = 32;
 template <typename M>
 __global__ void __launch_bounds__(kBlk) k_first_x(const M* o, double c, M* x, int64_t n,
@@ -59,8 +61,10 @@ __global__ void __launch_bounds__(kBlk) k_first_x(const M* o, double c, M* x, in
     if (j <= i) x[i * ld + j] = v;
   }
   __syncthreads();
-  for (int row = row0; row < kMirTile; row += kBlk / kMirTile)
-    if (i0 + col > j0 + row) x[(j0 + row) * ld + i0 + col] = sh[col][row];
+  for (int row = row0; row < kMirTile; row += kBlk / kMirTile) {
+    const int64_t i = j0 + row, j = i0 + col;
+    if (j > i) x[i * ld + j] = sh[col][row] + (j < n ? (M)0 * o[i * ld + j] : (M)0);
+  }
 }
 
 // Q = a0 I + a1 X + a2 T on the N x N block (T = X^2), zero elsewhere; q may be t.
