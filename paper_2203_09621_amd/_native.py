@@ -201,10 +201,11 @@ def _dev(t, name):
 _DTYPE, _IS_CUDA, _SHAPE = attrgetter("dtype"), attrgetter("is_cuda"), attrgetter("shape")
 
 
-def _devs(ts, name):
+def _devs(ts, name, count=None):
     """The pointer array of a list of tensors with the checks of _dev on each.  Whole
     lists go through C-level accessors (a batch passes tens of thousands of tensors);
-    a list that fails is taken one by one, for the error of its first bad entry."""
+    a list that fails is taken one by one, for the error of its first bad entry.
+    count: entries of the array, NULL past the end of the list."""
     torch = _torch()
     T = torch.Tensor
     ok = (all(issubclass(c, T) for c in set(map(type, ts)))
@@ -212,6 +213,10 @@ def _devs(ts, name):
           and all(map(_IS_CUDA, ts)) and all(map(T.is_contiguous, ts))
           and all(len(s) == 2 and s[0] == s[1] for s in set(map(_SHAPE, ts))))
     ptrs = list(map(T.data_ptr, ts)) if ok else [_dev(t, name).value for t in ts]
+    if count is not None:
+        if len(ptrs) > count:
+            raise IndexError(f"more {name} entries than problems")
+        ptrs += [0] * (count - len(ptrs))
     return (c_void_p * len(ptrs)).from_buffer(array("Q", ptrs)) if ptrs else (c_void_p * 0)()
 
 
@@ -529,8 +534,8 @@ def dmpt_batch_response(batch: c_void_p, H0s, H1s, P0s=None, P1s=None):
     st = (DmptProblemStats * count)()
     ms = c_double(0.0)
     status = LIB.dmpt_batch_response(
-        batch, _devs(H0s, "H0"), _devs(flat_h1, "H1"), _devs(P0s, "P0"), _devs(flat_p1, "P1"),
-        st, byref(ms))
+        batch, _devs(H0s, "H0"), _devs(flat_h1, "H1"), _devs(P0s, "P0", count),
+        _devs(flat_p1, "P1"), st, byref(ms))
     stats = _problem_stats(st)
     _check(status, {"problems": stats})
     return P0s, P1s, stats, ms.value

@@ -1,0 +1,49 @@
+"""What the batch entry point hands to the library: the arrays hold an entry for every
+problem, whatever the length and kind of the lists they are made from."""
+import pytest
+import torch
+
+from paper_2203_09621_amd import _native as nat
+
+
+class _Fake(torch.Tensor):
+    """A CPU tensor that claims to lie on the device."""
+    is_cuda = True
+
+
+def _t(n):
+    return torch.zeros(n, n, dtype=torch.float64).as_subclass(_Fake)
+
+
+@pytest.fixture
+def passed(monkeypatch):
+    """The lists of the four pointer arrays of the last call."""
+    seen = []
+
+    def response(batch, *args):
+        seen[:] = [list(a) for a in args[:4]]
+        return 0
+
+    monkeypatch.setattr(nat.LIB, "dmpt_batch_response", response)
+    return seen
+
+
+def _batch(count=3):
+    return [_t(2 + p) for p in range(count)], [[_t(2 + p)] * (1 + p % 2) for p in range(count)]
+
+
+@pytest.mark.parametrize("given", [0, 1, 2, 3])
+def test_missing_p0_entries_are_null(passed, given):
+    """P0 may be left out: a list shorter than the batch, or an empty one, is no error,
+    and the problems past its end write no P0."""
+    H0s, H1s = _batch()
+    P0s = [_t(2 + p) for p in range(given)]
+    nat.dmpt_batch_response(None, H0s, H1s, P0s=P0s)
+    assert passed[2] == [t.data_ptr() for t in P0s] + [None] * (3 - given)
+
+
+def test_too_many_p0_entries_are_refused(passed):
+    H0s, H1s = _batch()
+    with pytest.raises(IndexError):
+        nat.dmpt_batch_response(None, H0s, H1s, P0s=[_t(2)] * 4)
+    assert not passed
