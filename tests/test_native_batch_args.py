@@ -47,3 +47,14 @@ def test_too_many_p0_entries_are_refused(passed):
     with pytest.raises(IndexError):
         nat.dmpt_batch_response(None, H0s, H1s, P0s=[_t(2)] * 4)
     assert not passed
+
+
+def test_iterators_are_walked_once(passed):
+    H0s, H1s = _batch()
+    P0s = [_t(2 + p) for p in range(3)]
+    P1s = [[_t(2 + p)] * (1 + p % 2) for p in range(3)]
+    nat.dmpt_batch_response(None, H0s, (iter(h) for h in H1s), P0s=iter(P0s),
+                            P1s=(iter(p) for p in P1s))
+    assert passed[1] == [t.data_ptr() for h in H1s for t in h]
+    assert passed[2] == [t.data_ptr() for t in P0s]
+    assert passed[3] == [t.data_ptr() for p in P1s for t in p]
