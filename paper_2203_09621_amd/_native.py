@@ -532,6 +532,8 @@ def dmpt_batch_response(batch: c_void_p, H0s, H1s, P0s=None, P1s=None):
     if P1s is None:
         P1s = [[torch.empty_like(h) for h in hs] for hs in H1s]
     flat_p1 = [p for ps in P1s for p in ps]
+    if len(flat_p1) < len(flat_h1):              # the library reads one for every H1
+        raise ValueError("fewer P1 entries than H1 entries")
     st = (DmptProblemStats * count)()
     ms = c_double(0.0)
     status = LIB.dmpt_batch_response(

@@ -58,3 +58,11 @@ def test_iterators_are_walked_once(passed):
     assert passed[1] == [t.data_ptr() for h in H1s for t in h]
     assert passed[2] == [t.data_ptr() for t in P0s]
     assert passed[3] == [t.data_ptr() for p in P1s for t in p]
+
+
+@pytest.mark.parametrize("P1s", [[], [[_t(2)], [_t(3)], [_t(4)]]])
+def test_too_few_p1_entries_are_refused(passed, P1s):
+    H0s, H1s = _batch()
+    with pytest.raises(ValueError):
+        nat.dmpt_batch_response(None, H0s, H1s, P1s=P1s)
+    assert not passed
