@@ -574,20 +574,24 @@ dmpt_status dmpt_init(dmpt_ctx** out, const double* H0, int64_t N, int64_t Nocc,
     }
     e = hipMemcpy(tab, stage.data(), stage.size(), hipMemcpyHostToDevice);
   }
+  // (on the context's stream, which need not be ordered behind the null stream)
+  auto clear = [&](void* p, size_t bytes) {
+    if (e == hipSuccess) e = hipMemsetAsync(p, 0, bytes, c->stream);
+  };
+  clear(c->st, sizeof(LayerState));
   // outputs of the adjoint products leave the pad columns untouched
-  if (e == hipSuccess && c->ckpt) {
-    e = hipMemset(c->t2, 0, mat * eb);
-    for (int j = 0; j < k_max && j < 3 && e == hipSuccess; ++j) {
-      e = hipMemset(c->t1[j], 0, mat * eb);
-      if (e == hipSuccess) e = hipMemset(c->t3[j], 0, mat * eb);
+  if (c->ckpt) {
+    clear(c->t2, mat * eb);
+    for (int j = 0; j < k_max && j < 3; ++j) {
+      clear(c->t1[j], mat * eb);
+      clear(c->t3[j], mat * eb);
     }
   }
   // the products never write the pad columns of X and X1: they must start at zero
-  if (e == hipSuccess) e = hipMemset(c->st, 0, sizeof(LayerState));
-  if (e == hipSuccess && c->x) e = hipMemset(c->x, 0, mat * eb);
-  for (int j = 0; j < k_max && e == hipSuccess; ++j) {
-    e = hipMemset(c->s1buf[j][0], 0, mat * eb);
-    if (e == hipSuccess) e = hipMemset(c->s1buf[j][1], 0, mat * eb);
+  if (c->x) clear(c->x, mat * eb);
+  for (int j = 0; j < k_max; ++j) {
+    clear(c->s1buf[j][0], mat * eb);
+    clear(c->s1buf[j][1], mat * eb);
   }
   if (e != hipSuccess) return bail(DMPT_EHIP, std::string("allocation: ") + hipGetErrorString(e));
   // one pinned block: the state's copy, flags, progress (coherent: kernels write it)
