@@ -619,7 +619,8 @@ hipError_t enqueue_response(dmpt_batch* b, hipStream_t s) {
   // The launches of the small problems beside each other (each is a chain of
   // layers on as many CUs as it has problems: 0.15 to 0.9 ms for 400 to 900
   // problems, 0.3 to 0.5 ms for a few), and all of them before the layered
-  // problems, whose launches want every CU.
+  // problems, whose launches want every CU (beside them, joined before the outputs,
+  // is no faster: the branches of the graph cost as much as they hide).
   const int nt = (int)b->tiny.size(), sides = std::min(nt - 1, kTinySides);
   if (sides > 0) e = hipEventRecord(b->fork, s);
   for (int i = 0; i < sides && e == hipSuccess; ++i) e = hipStreamWaitEvent(b->side[i], b->fork, 0);
@@ -757,6 +758,25 @@ dmpt_status dmpt_batch_init(dmpt_batch** out, int32_t count, const int64_t* N, c
     batch_free(b);
     return bfail(s, m);
   };
+  // Small problems as one workgroup each (k_tiny), or layer by layer with the others.
+  // Their own launches come before the layered ones and take 0.1 ms for one
+  // configuration and up to 0.8 ms for several, whose streams fork and join in the
+  // graph; in the layered launches each is 1 + k more items, which cost next to nothing
+  // where a round has room.  So they leave a mixed batch only if it then saves two
+  // rounds of the launch, counted in pairs of 128-row tiles.  ms per response, split
+  // FP16, k = 1 to 3, as workgroups / layer by layer: 16 problems of N = 32 .. 128: 2.16 /
+  // 1.45; 128: 2.86 / 2.72 (one round); 256: 3.22 / 3.82 (three); 256 of N = 32 .. 160:
+  // 4.68 / 4.29 (one); 512: 6.04 / 7.36 (four); 512 of N = 90 .. 140: 7.62 / 8.01 (two);
+  // 64 of N = 16 .. 1024: 16.8 / 15.9 (none).
+  int64_t pairs_large = 0, pairs_small = 0;
+  for (int p = 0; p < count; ++p) {
+    const int64_t T = (N[p] + 127) / 128;
+    (tiny_blocks(N[p], k[p]) ? pairs_small : pairs_large) += (1 + k[p]) * ((T * (T + 1) / 2 + 1) / 2);
+  }
+  auto rounds = [&](int64_t pairs) { return (pairs + b->cus - 1) / b->cus; };
+  const bool split_off =
+      pairs_large == 0 || rounds(pairs_large + pairs_small) - rounds(pairs_large) >= 2;
+  auto blocks_of = [&](int p) { return split_off ? tiny_blocks(N[p], k[p]) : 0; };
   // sizes, block tables, sub-allocation offsets
   b->hp.resize(count);
   std::vector<int> order, first_h1(count);
@@ -764,12 +784,12 @@ dmpt_status dmpt_batch_init(dmpt_batch** out, int32_t count, const int64_t* N, c
   for (int p = 0; p < count; ++p) {
     first_h1[p] = h1;
     h1 += k[p];
-    if (!tiny_blocks(N[p], k[p])) order.push_back(p);
+    if (!blocks_of(p)) order.push_back(p);
   }
   b->n_layered = (int)order.size();
   for (int p = 0; p < count; ++p)
-    if (tiny_blocks(N[p], k[p])) order.push_back(p);
-  auto config = [&](int p) { return 4 * tiny_blocks(N[p], k[p]) + k[p]; };
+    if (blocks_of(p)) order.push_back(p);
+  auto config = [&](int p) { return 4 * blocks_of(p) + k[p]; };
   std::stable_sort(order.begin() + b->n_layered, order.end(),
                    [&](int x, int y) { return config(x) > config(y); });   // longest first
   size_t f32 = 0, u16 = 0;
@@ -779,7 +799,7 @@ dmpt_status dmpt_batch_init(dmpt_batch** out, int32_t count, const int64_t* N, c
     BatchProblem& q = b->hp[i];
     memset(&q, 0, sizeof(q));
     q.n = N[p];
-    q.np = layered ? (N[p] + 255) / 256 * 256 : 32 * tiny_blocks(N[p], k[p]);
+    q.np = layered ? (N[p] + 255) / 256 * 256 : 32 * blocks_of(p);
     q.ld = q.np;
     q.nocc = (double)Nocc[p];
     q.k = k[p];
@@ -792,9 +812,8 @@ dmpt_status dmpt_batch_init(dmpt_batch** out, int32_t count, const int64_t* N, c
       for (int bi = 0; bi < nob; ++bi)
         for (int bj = 0; bj < nob; ++bj) b->ob.push_back(OutBlock{i, j, bi, bj});
     if (!layered) {
-      if (b->tiny.empty() || b->tiny.back().nf != tiny_blocks(N[p], k[p]) ||
-          b->tiny.back().k != k[p])
-        b->tiny.push_back({tiny_blocks(N[p], k[p]), k[p], i - b->n_layered, 0});
+      if (b->tiny.empty() || b->tiny.back().nf != blocks_of(p) || b->tiny.back().k != k[p])
+        b->tiny.push_back({blocks_of(p), k[p], i - b->n_layered, 0});
       ++b->tiny.back().count;
       continue;
     }
