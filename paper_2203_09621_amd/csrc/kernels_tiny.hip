@@ -206,7 +206,8 @@ __global__ void __launch_bounds__(tiny_waves(NF) * kWave)
     st.max_layers = a.max_layers;
     st.n = st.converged = 0;
     st.error = error;
-    c1.done = st.done = error != 0;
+    // (a single problem runs its first layer before the error stops it, as layer by layer)
+    c1.done = st.done = H0 && error != 0;
     st.d0 = st.d0_layer = st.x_computed = st.upd_s0 = st.d0_now = st.sigma_cur = 0;
     st.order2_slot = -1;
     for (int i = 0; i < 4; ++i) {

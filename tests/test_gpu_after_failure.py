@@ -37,3 +37,26 @@ def test_response_after_a_failed_one(precision, n, bad, k):
         dm.dmpt_destroy(used)
     assert all(torch.equal(a, b) for a, b in zip(*out))
     assert np.isfinite(out[1][0].cpu().numpy()).all() and st is not None
+
+
+@pytest.mark.parametrize("precision", ["split_fp16", "split_bf16"])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_statistics_of_a_failed_small_response(precision, value):
+    """A problem that runs as one workgroup fails with the statistics of the layer by
+    layer path (which per-launch timing keeps)."""
+    import torch
+
+    import paper_2203_09621_amd as dm
+    from workloads import dense_gapped_problem
+
+    p = dense_gapped_problem(64, 32, 0.8, 31, h1="dense", k=2)
+    p.H1[1][5, 5] = value
+    got = []
+    for timing in (False, True):
+        with pytest.raises(dm.DmptError) as exc:
+            dm.solve(torch.from_numpy(p.H0).cuda(), [torch.from_numpy(h).cuda() for h in p.H1],
+                     p.nocc, precision=precision, timing=timing)
+        st = exc.value.stats
+        got.append([exc.value.status] + [st[key] for key in (
+            "layers", "d0_layer", "d1_layer", "converged", "sigma", "eps1", "epsN", "n_s")])
+    assert got[0][0] == -5 and got[0] == got[1]
