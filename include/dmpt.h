@@ -73,9 +73,15 @@ typedef struct {
   int32_t precision;       /* dmpt_precision; default DMPT_SPLIT_FP16 */
   int32_t max_layers;      /* default 100, at most DMPT_MAX_LAYERS */
   int32_t check_symmetry;  /* nonzero: dmpt_init / dmpt_response verify exact symmetry (EASYM) */
-  int32_t poll_every;      /* layers the host enqueues ahead of the device's stop flag (0 = auto) */
+  int32_t poll_every;      /* layers the host enqueues ahead of the device's stop flag (0 = auto).
+                              Without meaning where a problem runs as one workgroup (below) */
   int32_t timing;          /* nonzero: time every layer-product launch with hipEvents on the
-                              context's stream (dmpt_stats.product_ms / product_launches) */
+                              context's stream (dmpt_stats.product_ms / product_launches).
+                              Split problems of N <= 96 with k <= 3 (N <= 128 with k = 1)
+                              otherwise run as one workgroup, without such launches: with
+                              timing on, with ckpt_every > 0 and in dmpt_response2 they run
+                              layer by layer, which gives the same results but takes
+                              several times as long (N = 64: 0.18 ms, layer by layer 1.2) */
   int32_t ckpt_every;      /* > 0: dmpt_response keeps (S, S1) every this many layers so that
                               dmpt_adjoint can run; 0 (default): no adjoint workspace */
   int32_t graph;           /* batched solves: nonzero (default) captures the whole response in
@@ -83,7 +89,8 @@ typedef struct {
   int32_t tile_threshold;  /* batched solves: < 0 (default) times the candidate thresholds at
                               init and keeps the fastest; >= 0 fixes it: problems whose size
                               padded to 256 is at most this use 128-row tiles, the others
-                              256-row tiles */
+                              256-row tiles (small problems that run as one workgroup
+                              each use neither) */
 } dmpt_options;
 
 typedef struct {
@@ -203,10 +210,13 @@ void dmpt_destroy(dmpt_ctx* ctx);
 
 /* ---- batched solves: many independent problems of different sizes ----
  * Algorithms 1-3 for `count` problems at once.  Problem p has N[p] orbitals,
- * Nocc[p] occupied states and k[p] in [1, DMPT_MAX_KB] perturbations.  All
+ * Nocc[p] occupied states and k[p] in [1, DMPT_MAX_KB] perturbations.  The
  * problems advance layer by layer together; each keeps its own sigma
- * sequence and stopping tests and stops on its own.  Split precisions only
- * (DMPT_SPLIT_BF16 / DMPT_SPLIT_FP16).  The tile size of each problem's
+ * sequence and stopping tests and stops on its own.  Small ones (N <= 96, or
+ * N <= 128 with k = 1) run as one workgroup each instead if the batch holds
+ * no others or so many of them that the others' launches get at least two
+ * rounds shorter; results are the same either way.  Split precisions only
+ * (DMPT_SPLIT_BF16 / DMPT_SPLIT_FP16).  The tile size of the layered problems'
  * products (256 or 128 rows) is chosen at init by timing candidate size
  * thresholds on this batch, unless options.tile_threshold fixes it.  With
  * options.graph (default) the whole response
@@ -244,9 +254,11 @@ dmpt_status dmpt_batch_response(dmpt_batch* batch, const double* const* H0,
                                 dmpt_problem_stats* st, double* ms);
 
 /* Tile classes the autotuner chose (or options.tile_threshold fixed):
- * problems with padded size <= *threshold use 128-row tiles; number of item
- * positions of each launch (a 128-row item holds two tiles that share a row
- * or a column band, or one). */
+ * layered problems with padded size <= *threshold use 128-row tiles; number of
+ * item positions of each launch (a 128-row item holds two tiles that share a
+ * row or a column band, or one).  Problems that run as one workgroup each have
+ * no items; in a batch of such problems alone nothing is tuned, and *threshold
+ * is the given one or 0. */
 dmpt_status dmpt_batch_info(const dmpt_batch* batch, int32_t* threshold, int32_t* n_items_256,
                             int32_t* n_items_128);
 
