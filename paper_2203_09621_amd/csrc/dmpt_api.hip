@@ -285,7 +285,7 @@ struct dmpt_ctx {
   int n_tblocks;
   double* part_tr;
   double* part;       // reduction partials
-  double* dscal;      // device scalars (traces)
+  double* dscal;      // device scalars (Gershgorin bounds)
   int32_t* dflag;
   TileItem* items[kMaxK + 1];
   int n_items[kMaxK + 1];

@@ -170,7 +170,7 @@ struct ProductArgs {
 struct TinyProblem {
   LayerState* state;
   const float* s_init;       // single problem: normalised S0, row stride ld
-  float* s_master;           // batch: FP32 masters, row stride ld (upper triangles written)
+  float* s_master;           // batch: FP32 masters, row stride ld (written in full)
   float* s1buf[kMaxKB][2];
   int64_t ld;
   double nocc;
@@ -205,10 +205,10 @@ std::vector<int32_t> balanced_rounds(const std::vector<int64_t>& cost, int grid,
 DirectTile direct_tile(dmpt_precision prec, int64_t n, int singles, int doubles, bool upper);
 inline int64_t direct_kext(int64_t n) { return (n + 63) / 64 * 64; }
 hipError_t launch_products(dmpt_precision prec, const ProductArgs& a, hipStream_t s);
-// Tile items of an Np x Np output for the single-product modes: upper tiles
-// (mode 1) or all tiles (mode 2), tile edge product_tile(prec).
+// Items of the single-product modes over T x T tiles of any edge: upper tiles
+// (mode 1) or all tiles (mode 2).
 void product_items(int T, int mode, TileItem* out);   // T (T + 1) / 2 or T * T entries
-// Fused split layer with 256- or 128-row tiles (a.probs set): the products of
+// Fused split layer with 256-, 128- or 64-row tiles (a.probs set): the products of
 // layer n and, in their epilogue, the layer update, the next split and the
 // per-item partial sums; sigma and the update flags come from each problem's
 // state, decided before the launch.

@@ -1109,7 +1109,8 @@ template <> struct Direct<double> {
 // the e-th taking element e; A and B use the same (lane group, e) -> k map.
 // WPE waves per SIMD (4 WPE / (WGM WGN) workgroups per CU).  Operands go
 // straight from global memory into LDS, STAGES stages of BK-wide k-tiles: the
-// loads of tile t + STAGES - 1 go out while tile t is multiplied.
+// loads of tile t + STAGES go out before the last step of tile t, whose
+// fragments every wave holds by then, into the stage that tile t leaves.
 //
 // FLUSH > 0: blocked accumulation.  The FP32 16x16x4 MFMA adds its four
 // products one at a time, each rounded to FP32 and then added with one more
@@ -1513,7 +1514,10 @@ hipError_t launch_products_fused(dmpt_precision prec, const ProductArgs& a,
 }
 
 hipError_t launch_products(dmpt_precision prec, const ProductArgs& a, hipStream_t s) {
-  // tiles cover [0, kdim)^2 exactly; rows must keep 16-byte alignment
+  // The items cover N rounded up to the tile edge (direct forms; kdim in the split
+  // forms and in contexts with checkpoints).  What lies beyond up to kdim is read up
+  // to kext and by the update, never written, and has to be zero before the first
+  // launch.  Rows must keep 16-byte alignment.
   if (a.kdim % product_tile(prec) != 0 || a.ld < a.kdim || a.ld % 8 != 0)
     return hipErrorInvalidValue;
   if (a.mode != 0 && (prec == DMPT_SPLIT_FP16 || prec == DMPT_SPLIT_BF16 || a.state))
