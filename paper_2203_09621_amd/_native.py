@@ -208,7 +208,8 @@ def _devs(ts, name, count=None):
     count: entries of the array, NULL past the end of the list."""
     torch = _torch()
     T = torch.Tensor
-    ts = list(ts)                                # an iterator is walked once
+    if not isinstance(ts, (list, tuple)):        # an iterator is walked once
+        ts = list(ts)
     ok = (all(issubclass(c, T) for c in set(map(type, ts)))
           and set(map(_DTYPE, ts)) <= {torch.float64}
           and all(map(_IS_CUDA, ts)) and all(map(T.is_contiguous, ts))
