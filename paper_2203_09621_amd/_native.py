@@ -506,6 +506,11 @@ def dmpt_selftest_mfma(stream=None) -> int:
     return detail.value
 
 
+class _Batch(c_void_p):
+    """A batch handle with the number of problems and of responses that it holds."""
+    problems = responses = 0
+
+
 def dmpt_batch_init(Ns, noccs, ks, precision: str = "split_bf16", max_layers: int = 100,
                     graph: bool = True, stream=None, tile_threshold: int = -1) -> c_void_p:
     """dmpt_batch_init: workspace and tile tuning for a batch of problems
@@ -516,9 +521,10 @@ def dmpt_batch_init(Ns, noccs, ks, precision: str = "split_bf16", max_layers: in
     o.max_layers = max_layers
     o.graph = int(graph)
     o.tile_threshold = int(tile_threshold)
-    b = c_void_p()
+    b = _Batch()
     _check(LIB.dmpt_batch_init(byref(b), count, (c_int64 * count)(*Ns), (c_int64 * count)(*noccs),
                                (c_int32 * count)(*ks), byref(o), _stream(stream)))
+    b.problems, b.responses = count, sum(ks)
     return b
 
 
@@ -535,6 +541,8 @@ def dmpt_batch_response(batch: c_void_p, H0s, H1s, P0s=None, P1s=None):
     flat_p1 = [p for ps in P1s for p in ps]
     if len(flat_p1) < len(flat_h1):              # the library reads one for every H1
         raise ValueError("fewer P1 entries than H1 entries")
+    if isinstance(batch, _Batch) and (count < batch.problems or len(flat_h1) < batch.responses):
+        raise ValueError("fewer H0 or H1 entries than the batch has problems or responses")
     st = (DmptProblemStats * count)()
     ms = c_double(0.0)
     status = LIB.dmpt_batch_response(

@@ -66,3 +66,18 @@ def test_too_few_p1_entries_are_refused(passed, P1s):
     with pytest.raises(ValueError):
         nat.dmpt_batch_response(None, H0s, H1s, P1s=P1s)
     assert not passed
+
+
+@pytest.mark.parametrize("drop_h0,drop_h1", [(1, 0), (0, 1), (3, 4)])
+def test_fewer_inputs_than_the_batch_holds_are_refused(passed, monkeypatch, drop_h0, drop_h1):
+    monkeypatch.setattr(nat.LIB, "dmpt_batch_init", lambda *args: 0)
+    monkeypatch.setattr(nat, "_stream", lambda s: None)
+    H0s, H1s = _batch()
+    batch = nat.dmpt_batch_init([2, 3, 4], [1, 1, 2], [len(h) for h in H1s])
+    nat.dmpt_batch_response(batch, H0s, H1s)
+    assert len(passed[0]) == 3 and len(passed[1]) == 4
+    passed.clear()
+    flat = [[h] for hs in H1s for h in hs]
+    with pytest.raises(ValueError):
+        nat.dmpt_batch_response(batch, H0s[:3 - drop_h0], flat[:4 - drop_h1])
+    assert not passed
